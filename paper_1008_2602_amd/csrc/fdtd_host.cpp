@@ -48,6 +48,8 @@ hipError_t launch_dft_back(const float* series, int64_t max_steps, const double*
 hipError_t launch_fft(const float* series, int64_t n_samples, int n_fft, double2* a, double2* b,
                       double2** result, hipStream_t st);
 hipError_t launch_fill_zero(float* p, int64_t n, hipStream_t st);
+hipError_t launch_pack(const void* src, int elem, int64_t pitch, uint32_t len, uint32_t col, uint32_t n,
+                       double scale, void* out, const int32_t* bad, int32_t* bad_out, hipStream_t st);
 // fdtd_noalloc.hip
 hipError_t noalloc_scratch(int device, void** out);
 hipError_t launch_fft_split(const double2* x, int nbins, double* out, hipStream_t st);
@@ -225,6 +227,12 @@ struct fdtd_grid {
     bool graph_failed = false;
     hipEvent_t sync_ev = nullptr;
 
+    // pinned host memory that results pass through on their way to the caller: one
+    // line holding the watchdog flag, then two halves filled in turn (read_out)
+    char* pin = nullptr;
+    size_t pin_half = 0;
+    hipEvent_t pin_ev[2] = {nullptr, nullptr};
+
     // batched calls led by this handle: their plans (tables in device memory and
     // a captured graph), most recently used kept
     uint64_t serial = 0;            // unique per handle created in this process
@@ -278,44 +286,114 @@ hipError_t copy_sync(fdtd_grid* g, void* dst, const void* src, size_t bytes, hip
     return hipStreamSynchronize(g->stream);
 }
 
-// Copy one field array between the packed host layout ((nx+1) nodes per row)
-// and the padded device layout (pitch nodes per row): one contiguous copy of
-// the padded array through a host staging buffer (the padding columns hold
-// zeros), repacked row by row on the host, with every value multiplied by
-// `scale` on the way.
-hipError_t copy_field_sync(fdtd_grid* g, void* dst, const void* src, hipMemcpyKind kind,
-                           float scale = 1.0f)
+// Copy one field array from the packed host layout ((nx+1) nodes per row) to the
+// padded device layout (pitch nodes per row): one contiguous copy of the padded
+// array through a host staging buffer (the padding columns hold zeros), repacked
+// row by row on the host.
+hipError_t put_field_sync(fdtd_grid* g, void* dst, const void* src)
 {
     const size_t nrow = (size_t)g->d.nx + 1, pitch = (size_t)g->pitch;
     const size_t rows = (size_t)(g->d.ny + 1) * (g->d.nz + 1);
     std::vector<float> stage(rows * pitch, 0.0f);
-    if (kind == hipMemcpyHostToDevice) {
-        const float* in = (const float*)src;
-        for (size_t r = 0; r < rows; ++r) {
-            float* o = stage.data() + r * pitch;
-            const float* x = in + r * nrow;
-            if (scale == 1.0f)
-                memcpy(o, x, nrow * 4);
-            else
-                for (size_t i = 0; i < nrow; ++i) o[i] = x[i] * scale;
+    const float* in = (const float*)src;
+    for (size_t r = 0; r < rows; ++r) memcpy(stage.data() + r * pitch, in + r * nrow, nrow * 4);
+    return copy_sync(g, dst, stage.data(), stage.size() * 4, hipMemcpyHostToDevice);
+}
+
+// One result on the device: `rows` rows of `len` elements (elem = 4: floats,
+// multiplied by `scale` in FP64; 8: raw words), `pitch` elements apart, wanted
+// packed at host address `out`.
+struct Piece {
+    const void* src;
+    int elem;
+    int64_t rows, len, pitch;
+    double scale;
+    void* out;
+};
+
+// The pinned buffer's halves hold a node plane, within these bounds; longer
+// results pass through in turns.  It is made with the handle, so that no getter
+// allocates: 2 MiB takes about 60 us over the host link and 512 KiB about 20 us,
+// both above the cost of a launch and a wait, and 1 MiB of pinned memory takes
+// 10-40 us to allocate.
+constexpr size_t kPinHalfMin = 512u << 10, kPinHalfMax = 2u << 20, kPinHead = 256;
+hipError_t make_pin(fdtd_grid* g)
+{
+    const size_t plane = (size_t)g->pitch * (g->d.ny + 1) * 4;
+    g->pin_half = (std::min(std::max(plane, kPinHalfMin), kPinHalfMax) + 255) & ~size_t(255);
+    hipError_t e = hipHostMalloc((void**)&g->pin, kPinHead + 2 * g->pin_half, hipHostMallocDefault);
+    for (int h = 0; h < 2 && e == hipSuccess; ++h)
+        e = hipEventCreateWithFlags(&g->pin_ev[h], hipEventDisableTiming);
+    return e;
+}
+
+// Bring results to the host after the work queued on the handle's stream, which
+// has finished when this returns.  The device packs the pieces into one pinned
+// half while the host copies the other one out.  With `bad`, also the watchdog
+// flag as it is then.
+int read_out(fdtd_grid* g, const Piece* pc, int npc, int32_t* bad = nullptr)
+{
+    struct Part {
+        char* to;
+        const char* from;
+        size_t bytes;
+    };
+    std::vector<Part> parts[2];
+    int q = 0;
+    int64_t done = 0;   // elements of piece q already queued
+    bool first = true;
+    int half = 0;
+    auto drain = [&](int h) -> int {
+        if (parts[h].empty()) return FDTD_OK;
+        HIP_OR_FAIL(hipEventSynchronize(g->pin_ev[h]));
+        for (const Part& p : parts[h]) memcpy(p.to, p.from, p.bytes);
+        parts[h].clear();
+        return FDTD_OK;
+    };
+    while (q < npc) {
+        char* base = g->pin + kPinHead + half * g->pin_half;
+        size_t used = 0;
+        while (q < npc) {
+            const Piece& p = pc[q];
+            const int64_t n = p.rows * p.len, left = n - done;
+            const int64_t fit = (int64_t)((g->pin_half - used) / p.elem);
+            const int64_t take = std::min(left, fit);
+            if (left > 0 && take <= 0) break;
+            if (take > 0) {
+                const int64_t r0 = done / p.len, col = done % p.len;
+                const bool flat = p.rows == 1 || p.pitch == p.len;
+                const char* src = (const char*)p.src + (flat ? done : r0 * p.pitch) * p.elem;
+                HIP_OR_FAIL(launch_pack(src, p.elem, flat ? take : p.pitch,
+                                        (uint32_t)(flat ? take : p.len), flat ? 0u : (uint32_t)col,
+                                        (uint32_t)take, p.scale, base + used,
+                                        bad && first ? g->bad_dev : nullptr,
+                                        bad && first ? (int32_t*)g->pin : nullptr, g->stream));
+                first = false;
+                parts[half].push_back(Part{(char*)p.out + done * p.elem, base + used, (size_t)take * p.elem});
+                used += ((size_t)take * p.elem + 15) & ~size_t(15);
+                used = std::min(used, g->pin_half);
+                done += take;
+            }
+            if (done == n) {
+                ++q;
+                done = 0;
+            } else {
+                break;
+            }
         }
-        hipError_t e = hipMemcpyAsync(dst, stage.data(), stage.size() * 4, kind, g->stream);
-        if (e != hipSuccess) return e;
-        return hipStreamSynchronize(g->stream);
+        HIP_OR_FAIL(hipEventRecord(g->pin_ev[half], g->stream));
+        half ^= 1;
+        if (int e = drain(half)) return e;
     }
-    hipError_t e = hipMemcpyAsync(stage.data(), src, stage.size() * 4, kind, g->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
-    if (e != hipSuccess) return e;
-    float* out = (float*)dst;
-    for (size_t r = 0; r < rows; ++r) {
-        const float* x = stage.data() + r * pitch;
-        float* o = out + r * nrow;
-        if (scale == 1.0f)
-            memcpy(o, x, nrow * 4);
-        else
-            for (size_t i = 0; i < nrow; ++i) o[i] = x[i] * scale;
+    if (int e = drain(half)) return e;
+    if (int e = drain(half ^ 1)) return e;
+    if (bad && first) {
+        // no element was asked for: the flag alone
+        HIP_OR_FAIL(hipMemcpyAsync(g->pin, g->bad_dev, 4, hipMemcpyDeviceToHost, g->stream));
+        HIP_OR_FAIL(hipStreamSynchronize(g->stream));
     }
-    return hipSuccess;
+    if (bad) *bad = *(const int32_t*)g->pin;
+    return FDTD_OK;
 }
 
 int64_t row_pitch(int nx) { return ((int64_t)nx + 1 + 31) / 32 * 32; }
@@ -1059,7 +1137,16 @@ int check_bad(fdtd_grid* g)
 {
     if (!g->finalized) return FDTD_OK;
     int32_t bad = 0;
-    HIP_OR_FAIL(copy_sync(g, &bad, g->bad_dev, 4, hipMemcpyDeviceToHost));
+    if (int e = read_out(g, nullptr, 0, &bad)) return e;
+    if (bad) return fail(FDTD_EUNSTABLE, "non-finite field value (unstable run or bad input)");
+    return FDTD_OK;
+}
+
+// read_out with the watchdog's verdict (the results are delivered either way).
+int read_checked(fdtd_grid* g, const Piece* pc, int npc)
+{
+    int32_t bad = 0;
+    if (int e = read_out(g, pc, npc, g->finalized ? &bad : nullptr)) return e;
     if (bad) return fail(FDTD_EUNSTABLE, "non-finite field value (unstable run or bad input)");
     return FDTD_OK;
 }
@@ -1193,6 +1280,7 @@ int fdtd_create_grid(const fdtd_grid_desc* desc, fdtd_grid** out)
             hipStreamSynchronize(g->stream) != hipSuccess)
             return bail(FDTD_EDEVICE, "coefficient upload failed");
     }
+    if (make_pin(g) != hipSuccess) return bail(FDTD_ENOMEM, "pinned host memory allocation failed");
     g->step_dev = (int64_t*)dev_alloc(g, 16);   // step count, field buffer index
     g->bad_dev = (int32_t*)dev_alloc(g, 4);
     if (!g->step_dev || !g->bad_dev) return bail(FDTD_ENOMEM, "counter allocation failed");
@@ -2186,11 +2274,12 @@ int fdtd_get_probe(fdtd_grid* g, int id, float* out, int64_t n)
     if (int e = check_grid(g)) return e;
     if (id < 0 || id >= (int)g->probes.size()) return fail(FDTD_EINVAL, "no probe %d", id);
     if (n < 0 || n > g->step || (!out && n > 0)) return fail(FDTD_EINVAL, "bad sample count %lld", (long long)n);
-    HIP_OR_FAIL(hipStreamSynchronize(g->stream));
-    if (n > 0)
-        HIP_OR_FAIL(copy_sync(g, out, g->prb_series + (size_t)id * g->d.max_steps, (size_t)n * 4,
-                              hipMemcpyDeviceToHost));
-    return check_bad(g);
+    if (n == 0) {
+        HIP_OR_FAIL(hipStreamSynchronize(g->stream));
+        return check_bad(g);
+    }
+    const Piece p{g->prb_series + (size_t)id * g->d.max_steps, 4, 1, n, n, 1.0, out};
+    return read_checked(g, &p, 1);
 }
 
 int fdtd_get_voltage(fdtd_grid* g, int id, double* out, int64_t n)
@@ -2198,21 +2287,24 @@ int fdtd_get_voltage(fdtd_grid* g, int id, double* out, int64_t n)
     if (int e = check_grid(g)) return e;
     if (id < 0 || id >= (int)g->vprobes.size()) return fail(FDTD_EINVAL, "no voltage probe %d", id);
     if (n < 0 || n > g->step || (!out && n > 0)) return fail(FDTD_EINVAL, "bad sample count %lld", (long long)n);
-    HIP_OR_FAIL(hipStreamSynchronize(g->stream));
-    if (n == 0) return check_bad(g);
+    if (n == 0) {
+        HIP_OR_FAIL(hipStreamSynchronize(g->stream));
+        return check_bad(g);
+    }
     const VoltageProbeH& v = g->vprobes[id];
     std::vector<float> ez((size_t)v.count * n);
-    for (int q = 0; q < v.count; ++q)
-        HIP_OR_FAIL(copy_sync(g, ez.data() + (size_t)q * n,
-                              g->prb_series + (size_t)(v.first + q) * g->d.max_steps,
-                              (size_t)n * 4, hipMemcpyDeviceToHost));
+    // the column's probes are consecutive rows of the series
+    const Piece p{g->prb_series + (size_t)v.first * g->d.max_steps, 4, v.count, n, g->d.max_steps, 1.0,
+                  ez.data()};
+    const int verdict = read_checked(g, &p, 1);
+    if (verdict != FDTD_OK && verdict != FDTD_EUNSTABLE) return verdict;
     // V = -sum_k Ez(k+1/2) dz, summed upwards in z
     for (int64_t s = 0; s < n; ++s) {
         double acc = 0.0;
         for (int q = 0; q < v.count; ++q) acc += (double)ez[(size_t)q * n + s];
         out[s] = -g->d.dz * acc;
     }
-    return check_bad(g);
+    return verdict;
 }
 
 int fdtd_get_dft(fdtd_grid* g, int id, double* re, double* im)
@@ -2222,15 +2314,15 @@ int fdtd_get_dft(fdtd_grid* g, int id, double* re, double* im)
     if (g->freqs.empty()) return fail(FDTD_ESTATE, "no DFT frequencies were set");
     if (!re || !im) return fail(FDTD_EINVAL, "null output");
     const int nf = (int)g->freqs.size();
-    HIP_OR_FAIL(hipStreamSynchronize(g->stream));
     if (!g->finalized) {
+        HIP_OR_FAIL(hipStreamSynchronize(g->stream));
         std::fill(re, re + nf, 0.0);
         std::fill(im, im + nf, 0.0);
         return FDTD_OK;
     }
-    HIP_OR_FAIL(copy_sync(g, re, g->dft_re + (size_t)id * nf, nf * 8, hipMemcpyDeviceToHost));
-    HIP_OR_FAIL(copy_sync(g, im, g->dft_im + (size_t)id * nf, nf * 8, hipMemcpyDeviceToHost));
-    return check_bad(g);
+    const Piece p[2] = {{g->dft_re + (size_t)id * nf, 8, 1, nf, nf, 1.0, re},
+                        {g->dft_im + (size_t)id * nf, 8, 1, nf, nf, 1.0, im}};
+    return read_checked(g, p, 2);
 }
 
 int fdtd_get_plane_dft(fdtd_grid* g, double* re, double* im)
@@ -2239,18 +2331,16 @@ int fdtd_get_plane_dft(fdtd_grid* g, double* re, double* im)
     if (g->plane_k < 0) return fail(FDTD_ESTATE, "no plane DFT was set");
     if (!re || !im) return fail(FDTD_EINVAL, "null output");
     const int nf = (int)g->plane_freqs.size();
-    const size_t row = (size_t)(g->d.nx + 1) * 8, prow = (size_t)g->pitch * 8;
     const size_t rows = (size_t)nf * (g->d.ny + 1);
-    HIP_OR_FAIL(hipStreamSynchronize(g->stream));
     if (!g->finalized) {
+        HIP_OR_FAIL(hipStreamSynchronize(g->stream));
         std::fill(re, re + rows * (g->d.nx + 1), 0.0);
         std::fill(im, im + rows * (g->d.nx + 1), 0.0);
         return FDTD_OK;
     }
-    HIP_OR_FAIL(hipMemcpy2DAsync(re, row, g->plane_re, prow, row, rows, hipMemcpyDeviceToHost, g->stream));
-    HIP_OR_FAIL(hipMemcpy2DAsync(im, row, g->plane_im, prow, row, rows, hipMemcpyDeviceToHost, g->stream));
-    HIP_OR_FAIL(hipStreamSynchronize(g->stream));
-    return check_bad(g);
+    const Piece p[2] = {{g->plane_re, 8, (int64_t)rows, g->d.nx + 1, g->pitch, 1.0, re},
+                        {g->plane_im, 8, (int64_t)rows, g->d.nx + 1, g->pitch, 1.0, im}};
+    return read_checked(g, p, 2);
 }
 
 int fdtd_probe_fft(fdtd_grid* g, int id, int n_fft, double* re, double* im)
@@ -2273,18 +2363,20 @@ int fdtd_probe_fft(fdtd_grid* g, int id, int n_fft, double* re, double* im)
     double2* res = nullptr;
     hipError_t e = launch_fft(g->prb_series + (size_t)id * g->d.max_steps, g->step, n_fft, a, b,
                               &res, g->stream);
-    std::vector<double2> h((size_t)n_fft / 2 + 1);
-    if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
-    if (e == hipSuccess)
-        e = copy_sync(g, h.data(), res, h.size() * sizeof(double2), hipMemcpyDeviceToHost);
+    // the buffer the last pass did not write holds the split bins
+    const int nbins = n_fft / 2 + 1;
+    double* split = (double*)(res == a ? b : a);
+    if (e == hipSuccess) e = launch_fft_split(res, nbins, split, g->stream);
+    int rc = FDTD_OK;
+    if (e == hipSuccess) {
+        const Piece p[2] = {{split, 8, 1, nbins, nbins, 1.0, re}, {split + nbins, 8, 1, nbins, nbins, 1.0, im}};
+        rc = read_checked(g, p, 2);
+    }
+    if (e != hipSuccess || rc != FDTD_OK) (void)hipStreamSynchronize(g->stream);
     temp_free(g, a);
     temp_free(g, b);
     if (e != hipSuccess) return fail(FDTD_EDEVICE, "probe FFT failed: %s", hipGetErrorString(e));
-    for (size_t k = 0; k < h.size(); ++k) {
-        re[k] = h[k].x;
-        im[k] = h[k].y;
-    }
-    return check_bad(g);
+    return rc;
 }
 
 int fdtd_probe_fft_noalloc(fdtd_grid* g, int id, int n_fft, double* re, double* im)
@@ -2340,20 +2432,19 @@ static float* comp_ptr(fdtd_grid* g, int comp)
     return g->f[par][6 + comp - FDTD_BX];
 }
 
+// `planes` node planes of a component from plane k on, packed, times `scale`.
+static Piece field_piece(fdtd_grid* g, int comp, int k, int planes, double scale, void* out)
+{
+    return Piece{comp_ptr(g, comp) + (size_t)k * g->pitch * (g->d.ny + 1), 4,
+                 (int64_t)planes * (g->d.ny + 1), g->d.nx + 1, g->pitch, scale, out};
+}
+
 int fdtd_get_field(fdtd_grid* g, int comp, float* out)
 {
     if (int e = check_grid(g)) return e;
     if (comp < 0 || comp > FDTD_BZ || !out) return fail(FDTD_EINVAL, "bad component or output");
-    HIP_OR_FAIL(hipStreamSynchronize(g->stream));
-    const double s = field_scale(comp);
-    if (s == 1.0) {
-        HIP_OR_FAIL(copy_field_sync(g, out, comp_ptr(g, comp), hipMemcpyDeviceToHost));
-        return FDTD_OK;
-    }
-    std::vector<float> h((size_t)g->nodes);
-    HIP_OR_FAIL(copy_field_sync(g, h.data(), comp_ptr(g, comp), hipMemcpyDeviceToHost));
-    for (size_t t = 0; t < h.size(); ++t) out[t] = (float)((double)h[t] * s);
-    return FDTD_OK;
+    const Piece p = field_piece(g, comp, 0, g->d.nz + 1, field_scale(comp), out);
+    return read_out(g, &p, 1);
 }
 
 int fdtd_get_plane(fdtd_grid* g, int comp, int k, float* out)
@@ -2361,17 +2452,8 @@ int fdtd_get_plane(fdtd_grid* g, int comp, int k, float* out)
     if (int e = check_grid(g)) return e;
     if (comp < 0 || comp > FDTD_BZ || !out) return fail(FDTD_EINVAL, "bad component or output");
     if (k < 0 || k > g->d.nz) return fail(FDTD_EINVAL, "plane %d is outside 0..nz", k);
-    HIP_OR_FAIL(hipStreamSynchronize(g->stream));
-    const size_t row = (size_t)(g->d.nx + 1) * 4, prow = (size_t)g->pitch * 4;
-    const float* src = comp_ptr(g, comp) + (size_t)k * g->pitch * (g->d.ny + 1);
-    HIP_OR_FAIL(hipMemcpy2DAsync(out, row, src, prow, row, (size_t)g->d.ny + 1,
-                                 hipMemcpyDeviceToHost, g->stream));
-    HIP_OR_FAIL(hipStreamSynchronize(g->stream));
-    const double sc = field_scale(comp);
-    const size_t nn = (size_t)(g->d.nx + 1) * (g->d.ny + 1);
-    if (sc != 1.0)
-        for (size_t t = 0; t < nn; ++t) out[t] = (float)((double)out[t] * sc);
-    return check_bad(g);
+    const Piece p = field_piece(g, comp, k, 1, field_scale(comp), out);
+    return read_checked(g, &p, 1);
 }
 
 int fdtd_set_field(fdtd_grid* g, int comp, const float* in)
@@ -2421,7 +2503,7 @@ int fdtd_set_field(fdtd_grid* g, int comp, const float* in)
             }
         }
     HIP_OR_FAIL(hipStreamSynchronize(g->stream));
-    HIP_OR_FAIL(copy_field_sync(g, comp_ptr(g, comp), h.data(), hipMemcpyHostToDevice));
+    HIP_OR_FAIL(put_field_sync(g, comp_ptr(g, comp), h.data()));
     return FDTD_OK;
 }
 
@@ -2443,28 +2525,28 @@ int fdtd_save_state(fdtd_grid* g, void* host_buf, int64_t bytes)
     if (int e = check_grid(g)) return e;
     if (!host_buf || bytes < fdtd_state_bytes(g)) return fail(FDTD_EINVAL, "buffer too small");
     if (int e = finalize(g)) return e;
-    HIP_OR_FAIL(hipStreamSynchronize(g->stream));
     char* p = (char*)host_buf;
     int64_t hdr[kStateHeader / 8] = {0x4644544453544154ll, g->d.nx, g->d.ny, g->d.nz, g->step,
                                      (int64_t)g->probes.size(), (int64_t)g->freqs.size(),
                                      g->d.max_steps, g->plane_k, (int64_t)g->plane_freqs.size()};
     memcpy(p, hdr, kStateHeader);
     p += kStateHeader;
+    std::vector<Piece> pc;
     for (int c = 0; c < 12; ++c) {
-        HIP_OR_FAIL(copy_field_sync(g, p, comp_ptr(g, c), hipMemcpyDeviceToHost));
+        pc.push_back(field_piece(g, c, 0, g->d.nz + 1, 1.0, p));
         p += g->nodes * 4;
     }
     const int64_t np = (int64_t)g->probes.size(), nf = (int64_t)g->freqs.size();
     if (np) {
-        HIP_OR_FAIL(copy_sync(g, p, g->prb_series, np * g->d.max_steps * 4, hipMemcpyDeviceToHost));
+        pc.push_back(Piece{g->prb_series, 4, 1, np * g->d.max_steps, np * g->d.max_steps, 1.0, p});
         p += np * g->d.max_steps * 4;
     }
-    if (np && nf) {
-        HIP_OR_FAIL(copy_sync(g, p, g->dft_re, np * nf * 8, hipMemcpyDeviceToHost));
-        p += np * nf * 8;
-        HIP_OR_FAIL(copy_sync(g, p, g->dft_im, np * nf * 8, hipMemcpyDeviceToHost));
-        p += np * nf * 8;
-    }
+    if (np && nf)
+        for (const double* a : {g->dft_re, g->dft_im}) {
+            pc.push_back(Piece{a, 8, 1, np * nf, np * nf, 1.0, p});
+            p += np * nf * 8;
+        }
+    if (int e = read_out(g, pc.data(), (int)pc.size())) return e;
     if (g->plane_k >= 0) {
         // the ring is always folded when a call returns: the accumulators are the state
         const int64_t pn = (int64_t)g->plane_freqs.size() * (g->d.nx + 1) * (g->d.ny + 1);
@@ -2491,7 +2573,7 @@ int fdtd_load_state(fdtd_grid* g, const void* host_buf, int64_t bytes)
     HIP_OR_FAIL(hipStreamSynchronize(g->stream));
     g->step = hdr[4];
     for (int c = 0; c < 12; ++c) {
-        HIP_OR_FAIL(copy_field_sync(g, comp_ptr(g, c), p, hipMemcpyHostToDevice));
+        HIP_OR_FAIL(put_field_sync(g, comp_ptr(g, c), p));
         p += g->nodes * 4;
     }
     const int64_t np = (int64_t)g->probes.size(), nf = (int64_t)g->freqs.size();
@@ -2580,6 +2662,9 @@ int fdtd_destroy_grid(fdtd_grid* g)
     if (!g) return FDTD_OK;
     if (g->stream) (void)hipStreamSynchronize(g->stream);
     for (hipEvent_t e : g->ev_pool) (void)hipEventDestroy(e);
+    if (g->pin) (void)hipHostFree(g->pin);
+    for (hipEvent_t e : g->pin_ev)
+        if (e) (void)hipEventDestroy(e);
     if (g->graph_exec) (void)hipGraphExecDestroy(g->graph_exec);
     if (g->sync_ev) (void)hipEventDestroy(g->sync_ev);
     for (BatchPlan* p : g->plans) free_plan(g, p);

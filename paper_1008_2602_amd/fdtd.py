@@ -269,7 +269,9 @@ def fdtd_get_plane_dft(g, ny: int, nx: int) -> np.ndarray:
     re = np.zeros((nf, ny + 1, nx + 1))
     im = np.zeros((nf, ny + 1, nx + 1))
     _check(_lib.fdtd_get_plane_dft(g, _ptr(re), _ptr(im)))
-    return re + 1j * im
+    out = np.empty(re.shape, np.complex128)
+    out.real, out.imag = re, im
+    return out
 
 
 def fdtd_get_plane(g, comp: int, k: int, ny: int, nx: int) -> np.ndarray:
