@@ -33,6 +33,9 @@ hipError_t launch_field_step2_material(int tile_y, int mode, const BoardDev* boa
                                        const TileRef* tiles, int ntiles, int rel, int flip,
                                        bool wide, bool plane, bool nt, hipStream_t st);
 int field_step2_material_occupancy(int tile_y, int mode, bool wide);
+// fdtd_kernels_brick.hip
+int pick_brick(int nx, int ny, int nz, int cus);
+hipError_t launch_brick(int q, const BoardDev& b, int par, int rel, bool wide, bool plane, hipStream_t st);
 hipError_t launch_advance(BoardDev* boards, int nb, const int64_t* n, hipStream_t st);
 hipError_t launch_advance_one(int64_t* step, int64_t n, int64_t launches, hipStream_t st);
 hipError_t launch_eps_step(const BoardDev* board, int nx, int ny, int nz, int64_t plane_bytes,
@@ -213,6 +216,9 @@ struct fdtd_grid {
     bool finalized = false;
     int64_t step = 0;
     int tile_x = 64, tile_y = 14, tile_steps = 2;
+    bool tile_set = false;  // by fdtd_set_tile
+    int brick = -1;         // >= 0: pairs of steps run the small-board kernel in this brick shape
+    int par0 = 0;           // field copy at the start of the launches being enqueued (bricks)
     int cus = 0;            // compute units of the device
     int64_t step_bytes = 0;
 
@@ -223,7 +229,8 @@ struct fdtd_grid {
     int64_t timed_launches = 0;
 
     // graph of kGraphChunk steps (field launches + counter advance), replayed by step_n
-    hipGraphExec_t graph_exec = nullptr;
+    // (bricks: one per field copy it starts from; else [0])
+    hipGraphExec_t graph_exec[2] = {nullptr, nullptr};
     bool graph_failed = false;
     hipEvent_t sync_ev = nullptr;
 
@@ -1573,9 +1580,10 @@ static int upload_tiles(fdtd_grid* g)
         if (int e = upload_list(g, kOddX, kOddY, 1, &g->tiles1_dev, &g->ntiles1, &g->tiles1_cap))
             return e;
     HIP_OR_FAIL(copy_sync(g, g->board_dev, &b, sizeof(BoardDev), hipMemcpyHostToDevice));
-    if (g->graph_exec) {
-        (void)hipGraphExecDestroy(g->graph_exec);
-        g->graph_exec = nullptr;
+    g->brick = g->tile_set || g->node_pass ? -1 : pick_brick(g->d.nx, g->d.ny, g->d.nz, g->cus);
+    for (hipGraphExec_t& e : g->graph_exec) {
+        if (e) (void)hipGraphExecDestroy(e);
+        e = nullptr;
     }
     g->graph_failed = false;
     return FDTD_OK;
@@ -1604,6 +1612,7 @@ int fdtd_set_tile(fdtd_grid* g, int tile_x, int tile_y, int steps)
     g->tile_x = tile_x;
     g->tile_y = tile_y;
     g->tile_steps = steps;
+    g->tile_set = true;
     return g->finalized ? upload_tiles(g) : FDTD_OK;
 }
 
@@ -1664,6 +1673,9 @@ static int enqueue_launch(fdtd_grid* g, bool single, int rel, int flip)
         if (int e = record_event(g)) return e;
     if (g->mat)
         HIP_OR_FAIL(single ? node_step(g, rel, flip, g->stream) : material_pair(g, rel, flip, g->stream));
+    else if (!single && g->brick >= 0)
+        HIP_OR_FAIL(launch_brick(g->brick, g->board_host, (g->par0 + flip) & 1, rel, g->wide,
+                                 g->plane_k >= 0, g->stream));
     else if (single && g->tile_steps == 2)
         HIP_OR_FAIL(launch_pass(kOddX, kOddY, 1, g->board_dev, g->tiles1_dev, g->ntiles1, rel, flip,
                                 g->wide, g->plane_k >= 0, false, g->stream));
@@ -1712,7 +1724,9 @@ static int enqueue_steps(fdtd_grid* g, int64_t n, int64_t* launches)
 // every chunk.  Any failure leaves plain launches in use.
 static void build_graph(fdtd_grid* g)
 {
-    if (g->graph_exec || g->graph_failed) return;
+    // a brick launch names the field copy it reads
+    hipGraphExec_t& exec = g->graph_exec[g->brick >= 0 ? g->par0 : 0];
+    if (exec || g->graph_failed) return;
     g->graph_failed = true;
     if (!g->own_stream && g->stream == nullptr) return;
     hipGraph_t graph = nullptr;
@@ -1722,6 +1736,9 @@ static void build_graph(fdtd_grid* g)
     for (int l = 0; l < nl && ok; ++l)
         ok = (g->mat         ? material_pair(g, l * per, l & 1, g->stream)
               : g->node_pass ? node_step(g, l, l & 1, g->stream)
+              : g->brick >= 0
+                  ? launch_brick(g->brick, g->board_host, (g->par0 + l) & 1, l * per, g->wide,
+                                 g->plane_k >= 0, g->stream)
                              : launch_pass(g->tile_x, g->tile_y, per, g->board_dev, g->tiles_dev,
                                            g->ntiles, l * per, l & 1, g->wide, g->plane_k >= 0,
                                            stream_stores(&g, 1), g->stream)) == hipSuccess;
@@ -1729,10 +1746,10 @@ static void build_graph(fdtd_grid* g)
     if (ok) ok = fold_plane(g, -kGraphChunk, 0, g->stream) == FDTD_OK;
     const bool ended = hipStreamEndCapture(g->stream, &graph) == hipSuccess;
     if (ok && ended && graph &&
-        hipGraphInstantiate(&g->graph_exec, graph, nullptr, nullptr, 0) == hipSuccess)
+        hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) == hipSuccess)
         g->graph_failed = false;
     else
-        g->graph_exec = nullptr;
+        exec = nullptr;
     if (graph) (void)hipGraphDestroy(graph);
     (void)hipGetLastError();
 }
@@ -1747,27 +1764,42 @@ int fdtd_step_n(fdtd_grid* g, int64_t n)
     if (int e = finalize(g)) return e;
     if (n == 0) return FDTD_OK;
     int64_t done = 0, launches = 0;
-    if (!g->timing && n >= kGraphChunk) {
+    // plain launches up to step `to`: the kernels add the launch-relative step and
+    // buffer to the device counters, which advance after them; with a plane DFT
+    // the ring is folded at least every kPlaneRing steps
+    auto plain = [&](int64_t to) -> int {
+        while (done < to) {
+            const int64_t m = g->plane_k >= 0 ? std::min<int64_t>(to - done, kPlaneRing) : to - done;
+            int64_t l = 0;
+            g->par0 = (int)((g->buf + launches) & 1);
+            if (int e = enqueue_steps(g, m, &l)) return e;
+            HIP_OR_FAIL(launch_advance_one(g->step_dev, m, l, g->stream));
+            if (int e = fold_plane(g, -m, 0, g->stream)) return e;
+            launches += l;
+            done += m;
+        }
+        return FDTD_OK;
+    };
+    // A graph takes about 2 ms to capture and instantiate: the steps that run
+    // meanwhile are enqueued as plain launches first.  A brick launch (6 us and
+    // more on the device, 2.4 us to enqueue) gains nothing from a graph but the
+    // host's time, so short calls of such boards go without.
+    const int64_t first = g->brick >= 0 ? 32 * kGraphChunk : kGraphChunk;
+    const bool have = g->graph_exec[g->brick >= 0 ? g->buf : 0] != nullptr;
+    const bool graph = !g->timing && n >= kGraphChunk && (have || g->brick < 0 || n >= 2 * first);
+    if (graph && !have && n >= 2 * first)
+        if (int e = plain(first)) return e;
+    if (graph) {
+        g->par0 = (int)((g->buf + launches) & 1);
         build_graph(g);
-        if (g->graph_exec) {
+        if (hipGraphExec_t exec = g->graph_exec[g->brick >= 0 ? g->par0 : 0]) {
             for (; done + kGraphChunk <= n; done += kGraphChunk) {
-                HIP_OR_FAIL(hipGraphLaunch(g->graph_exec, g->stream));
+                HIP_OR_FAIL(hipGraphLaunch(exec, g->stream));
                 launches += kGraphChunk / (g->node_pass && !g->mat ? 1 : g->tile_steps);
             }
         }
     }
-    while (done < n) {
-        // kernels add the launch-relative step and buffer to the device counters,
-        // which the graphs above have already advanced; with a plane DFT the ring
-        // is folded at least every kPlaneRing steps
-        const int64_t m = g->plane_k >= 0 ? std::min<int64_t>(n - done, kPlaneRing) : n - done;
-        int64_t l = 0;
-        if (int e = enqueue_steps(g, m, &l)) return e;
-        HIP_OR_FAIL(launch_advance_one(g->step_dev, m, l, g->stream));
-        if (int e = fold_plane(g, -m, 0, g->stream)) return e;
-        launches += l;
-        done += m;
-    }
+    if (int e = plain(n)) return e;
     if (g->dft_f)
         HIP_OR_FAIL(launch_dft(g->prb_series, g->d.max_steps, g->dft_f, (int)g->freqs.size(),
                                (int)g->probes.size(), g->dt, g->step, g->step + n, g->dft_re,
@@ -2665,7 +2697,8 @@ int fdtd_destroy_grid(fdtd_grid* g)
     if (g->pin) (void)hipHostFree(g->pin);
     for (hipEvent_t e : g->pin_ev)
         if (e) (void)hipEventDestroy(e);
-    if (g->graph_exec) (void)hipGraphExecDestroy(g->graph_exec);
+    for (hipGraphExec_t e : g->graph_exec)
+        if (e) (void)hipGraphExecDestroy(e);
     if (g->sync_ev) (void)hipEventDestroy(g->sync_ev);
     for (BatchPlan* p : g->plans) free_plan(g, p);
     for (BatchPlan* p : g->retired) free_plan(g, p);
