@@ -48,14 +48,13 @@ hipError_t launch_dft(const float* series, int64_t max_steps, const double* freq
 hipError_t launch_dft_back(const float* series, int64_t max_steps, const double* freqs, int nf,
                            int np, double dt, const int64_t* step, int64_t back, double* re,
                            double* im, hipStream_t st);
-hipError_t launch_fft(const float* series, int64_t n_samples, int n_fft, double2* a, double2* b,
-                      double2** result, hipStream_t st);
+hipError_t launch_fft(const float* series, int64_t n_samples, int n_fft, double2* a, double* re, double* im,
+                      const int32_t* bad, int32_t* bad_out, hipStream_t st);
 hipError_t launch_fill_zero(float* p, int64_t n, hipStream_t st);
 hipError_t launch_pack(const void* src, int elem, int64_t pitch, uint32_t len, uint32_t col, uint32_t n,
                        double scale, void* out, const int32_t* bad, int32_t* bad_out, hipStream_t st);
 // fdtd_noalloc.hip
 hipError_t noalloc_scratch(int device, void** out);
-hipError_t launch_fft_split(const double2* x, int nbins, double* out, hipStream_t st);
 }  // namespace fdtd
 
 using namespace fdtd;
@@ -2375,6 +2374,30 @@ int fdtd_get_plane_dft(fdtd_grid* g, double* re, double* im)
     return read_checked(g, p, 2);
 }
 
+// Probe `id`'s spectrum with n_fft points of scratch `a`.  The bins go to the pinned
+// buffer as they are computed where it holds them all, else through `bins` (room
+// for n_fft + 2 doubles on the device).
+static int probe_spectrum(fdtd_grid* g, int id, int n_fft, double2* a, double* bins, double* re, double* im)
+{
+    const size_t nbins = (size_t)n_fft / 2 + 1;
+    const float* series = g->prb_series + (size_t)id * g->d.max_steps;
+    if (nbins * 16 > 2 * g->pin_half) {
+        HIP_OR_FAIL(launch_fft(series, g->step, n_fft, a, bins, bins + nbins, nullptr, nullptr, g->stream));
+        const Piece p[2] = {{bins, 8, 1, (int64_t)nbins, (int64_t)nbins, 1.0, re},
+                            {bins + nbins, 8, 1, (int64_t)nbins, (int64_t)nbins, 1.0, im}};
+        return read_checked(g, p, 2);
+    }
+    double* host = (double*)(g->pin + kPinHead);
+    HIP_OR_FAIL(launch_fft(series, g->step, n_fft, a, host, host + nbins, g->bad_dev, (int32_t*)g->pin,
+                           g->stream));
+    HIP_OR_FAIL(hipStreamSynchronize(g->stream));
+    memcpy(re, host, nbins * 8);
+    memcpy(im, host + nbins, nbins * 8);
+    if (*(const int32_t*)g->pin)
+        return fail(FDTD_EUNSTABLE, "non-finite field value (unstable run or bad input)");
+    return FDTD_OK;
+}
+
 int fdtd_probe_fft(fdtd_grid* g, int id, int n_fft, double* re, double* im)
 {
     if (int e = check_grid(g)) return e;
@@ -2384,30 +2407,14 @@ int fdtd_probe_fft(fdtd_grid* g, int id, int n_fft, double* re, double* im)
                     (long long)g->step);
     if (!re || !im) return fail(FDTD_EINVAL, "null output");
     if (int e = finalize(g)) return e;
-    HIP_OR_FAIL(hipStreamSynchronize(g->stream));
-    double2* a = (double2*)temp_alloc(g, (size_t)n_fft * sizeof(double2));
-    double2* b = (double2*)temp_alloc(g, (size_t)n_fft * sizeof(double2));
-    if (!a || !b) {
-        temp_free(g, a);
-        temp_free(g, b);
-        return fail(FDTD_ENOMEM, "FFT scratch allocation failed");
-    }
-    double2* res = nullptr;
-    hipError_t e = launch_fft(g->prb_series + (size_t)id * g->d.max_steps, g->step, n_fft, a, b,
-                              &res, g->stream);
-    // the buffer the last pass did not write holds the split bins
-    const int nbins = n_fft / 2 + 1;
-    double* split = (double*)(res == a ? b : a);
-    if (e == hipSuccess) e = launch_fft_split(res, nbins, split, g->stream);
-    int rc = FDTD_OK;
-    if (e == hipSuccess) {
-        const Piece p[2] = {{split, 8, 1, nbins, nbins, 1.0, re}, {split + nbins, 8, 1, nbins, nbins, 1.0, im}};
-        rc = read_checked(g, p, 2);
-    }
-    if (e != hipSuccess || rc != FDTD_OK) (void)hipStreamSynchronize(g->stream);
+    // scratch of the points and, where the pinned buffer is too small, of the bins
+    const size_t points = (size_t)n_fft * sizeof(double2);
+    const bool direct = ((size_t)n_fft / 2 + 1) * 16 <= 2 * g->pin_half;
+    char* a = (char*)temp_alloc(g, points + (direct ? 0 : points + 256));
+    if (!a) return fail(FDTD_ENOMEM, "FFT scratch allocation failed");
+    const int rc = probe_spectrum(g, id, n_fft, (double2*)a, (double*)(a + points), re, im);
+    if (rc != FDTD_OK) (void)hipStreamSynchronize(g->stream);   // the scratch may still be in use
     temp_free(g, a);
-    temp_free(g, b);
-    if (e != hipSuccess) return fail(FDTD_EDEVICE, "probe FFT failed: %s", hipGetErrorString(e));
     return rc;
 }
 
@@ -2423,27 +2430,19 @@ int fdtd_probe_fft_noalloc(fdtd_grid* g, int id, int n_fft, double* re, double* 
                     "n_fft %d exceeds the allocation-free maximum %d (use fdtd_probe_fft)", n_fft,
                     kNoAllocFftMax);
     if (!re || !im) return fail(FDTD_EINVAL, "null output");
-    const int nbins = n_fft / 2 + 1;
     if (!g->finalized) {
         // nothing stepped yet (set-up, which allocates, has not run): no samples
+        const int nbins = n_fft / 2 + 1;
         std::fill(re, re + nbins, 0.0);
         std::fill(im, im + nbins, 0.0);
         return FDTD_OK;
     }
     void* s = nullptr;
     HIP_OR_FAIL(noalloc_scratch(g->device, &s));
+    // the points in the first half of the scratch, the bins (at most 2^20 + 2
+    // doubles) in the second
     double2* a = (double2*)s;
-    double2* b = a + kNoAllocFftMax;
-    double2* res = nullptr;
-    HIP_OR_FAIL(launch_fft(g->prb_series + (size_t)id * g->d.max_steps, g->step, n_fft, a, b,
-                           &res, g->stream));
-    // the buffer the last pass did not write holds the split bins
-    double* split = (double*)(res == a ? b : a);
-    HIP_OR_FAIL(launch_fft_split(res, nbins, split, g->stream));
-    HIP_OR_FAIL(hipMemcpyAsync(re, split, (size_t)nbins * 8, hipMemcpyDeviceToHost, g->stream));
-    HIP_OR_FAIL(hipMemcpyAsync(im, split + nbins, (size_t)nbins * 8, hipMemcpyDeviceToHost, g->stream));
-    HIP_OR_FAIL(hipStreamSynchronize(g->stream));
-    return check_bad(g);
+    return probe_spectrum(g, id, n_fft, a, (double*)(a + kNoAllocFftMax), re, im);
 }
 
 static double field_scale(int comp)

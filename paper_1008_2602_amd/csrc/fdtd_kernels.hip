@@ -508,31 +508,101 @@ __global__ __launch_bounds__(256) void plane_fold(const float* __restrict__ ring
     }
 }
 
-// Zero-padded complex FP64 input for the probe FFT.
-__global__ void fft_load(const float* __restrict__ series, int64_t n_samples, int n_fft,
-                         double2* __restrict__ out)
+// Probe FFT (FP64): X[k] = sum_{s<N} e[s] exp(-2 pi i k s / n), n = n1 n2 a power of
+// two, in two launches (four-step): fft_columns transforms the n1-point columns
+// s = j1 n2 + j2 over j1 and turns them by exp(-2 pi i j2 k1 / n), fft_rows the
+// n2-point rows over j2, giving k = k1 + n1 k2.  Each block holds C = 2^lc columns
+// (rows) of 2^ln points in LDS and runs all their radix-2 passes there, in place
+// (decimation in frequency; the bit reversal is in the index a result is read
+// from).  One pass per launch over global memory took 17 dependent launches for
+// 65536 points, 45 us of launch latency for 2 MB of traffic.
+// Points are kept at slot j C + (c ^ (j mod C)), so that lanes running along j as
+// well as along c fall on different banks.
+constexpr int kFftTw = 1024;   // twiddles held in LDS; longer columns compute theirs
+
+__device__ __forceinline__ double2 cmul(double2 a, double2 b)
 {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n_fft) return;
-    out[s] = make_double2(s < n_samples ? (double)series[s] : 0.0, 0.0);
+    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
+// exp(-2 pi i t / 2^ln)
+__device__ __forceinline__ double2 fft_root(uint64_t t, int ln)
+{
+    double sn, cs;
+    sincospi(-2.0 * ((double)t / (double)(1ull << ln)), &sn, &cs);
+    return make_double2(cs, sn);
+}
+__device__ __forceinline__ int fft_slot(int j, int c, int lc) { return (j << lc) + (c ^ (j & ((1 << lc) - 1))); }
+
+// the C columns of 2^ln points in buf; call with the data in place and synchronised
+__device__ void fft_lds(double2* buf, double2* tw, int ln, int lc)
+{
+    const int n = 1 << ln, half_n = n >> 1;
+    const bool tab = half_n <= kFftTw;
+    if (tab)
+        for (int t = threadIdx.x; t < half_n; t += blockDim.x) tw[t] = fft_root(t, ln);
+    __syncthreads();
+    for (int lh = ln - 1; lh >= 0; --lh) {
+        const int half = 1 << lh;
+        for (int q = threadIdx.x; q < half_n << lc; q += blockDim.x) {
+            const int c = q & ((1 << lc) - 1), m = q >> lc, r = m & (half - 1);
+            const int j = ((m >> lh) << (lh + 1)) + r;
+            const int s0 = fft_slot(j, c, lc), s1 = fft_slot(j + half, c, lc);
+            const double2 u = buf[s0], v = buf[s1];
+            const int t = r << (ln - 1 - lh);
+            buf[s0] = make_double2(u.x + v.x, u.y + v.y);
+            buf[s1] = cmul(make_double2(u.x - v.x, u.y - v.y), tab ? tw[t] : fft_root(t, ln));
+        }
+        __syncthreads();
+    }
 }
 
-// One radix-2 Stockham pass (natural-order output after log2(n) passes):
-// for j < n/2 with span ns: v0 = x[j], v1 = x[j + n/2] * exp(-2 pi i (j mod ns) / (2 ns)),
-// y[(j/ns)*2ns + j%ns] = v0 + v1, y[... + ns] = v0 - v1.
-__global__ void fft_pass(const double2* __restrict__ x, double2* __restrict__ y, int n, int ns)
+template <int E>   // points per block
+__global__ __launch_bounds__(1024) void fft_columns(const float* __restrict__ series, int64_t n_samples,
+                                                    int l1, int l2, int lc, double2* __restrict__ out)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n / 2) return;
-    const int r = j % ns;
-    double sn, cs;
-    sincospi(-(double)r / (double)ns, &sn, &cs);
-    const double2 a = x[j];
-    const double2 b0 = x[j + n / 2];
-    const double2 b = make_double2(b0.x * cs - b0.y * sn, b0.x * sn + b0.y * cs);
-    const int o = (j / ns) * 2 * ns + r;
-    y[o] = make_double2(a.x + b.x, a.y + b.y);
-    y[o + ns] = make_double2(a.x - b.x, a.y - b.y);
+    __shared__ double2 buf[E];
+    __shared__ double2 tw[kFftTw];
+    const int n1 = 1 << l1, c0 = blockIdx.x << lc, C = 1 << lc;
+    for (int q = threadIdx.x; q < n1 << lc; q += blockDim.x) {
+        const int c = q & (C - 1), j = q >> lc;
+        const int64_t s = ((int64_t)j << l2) + c0 + c;
+        buf[fft_slot(j, c, lc)] = make_double2(s < n_samples ? (double)series[s] : 0.0, 0.0);
+    }
+    fft_lds(buf, tw, l1, lc);   // synchronises first
+    for (int q = threadIdx.x; q < n1 << lc; q += blockDim.x) {
+        const int c = q & (C - 1), k = q >> lc;
+        const int j = l1 ? (int)(__brev((unsigned)k) >> (32 - l1)) : 0;
+        const uint64_t turn = (uint64_t)(c0 + c) * (uint64_t)k;   // < n
+        out[((int64_t)k << l2) + c0 + c] = cmul(buf[fft_slot(j, c, lc)], fft_root(turn, l1 + l2));
+    }
+}
+
+// bins 0 .. n/2 split into re and im (host or device memory); with `bad` also the
+// watchdog flag
+template <int E>
+__global__ __launch_bounds__(1024) void fft_rows(const double2* __restrict__ in, int l1, int l2, int lc,
+                                                 double* __restrict__ re, double* __restrict__ im,
+                                                 const int32_t* __restrict__ bad, int32_t* __restrict__ bad_out)
+{
+    __shared__ double2 buf[E];
+    __shared__ double2 tw[kFftTw];
+    if (bad_out && blockIdx.x == 0 && threadIdx.x == 0) *bad_out = *bad;
+    const int n2 = 1 << l2, c0 = blockIdx.x << lc, C = 1 << lc;
+    for (int q = threadIdx.x; q < n2 << lc; q += blockDim.x) {
+        const int j = q & (n2 - 1), c = q >> l2;   // along the row
+        buf[fft_slot(j, c, lc)] = in[((int64_t)(c0 + c) << l2) + j];
+    }
+    fft_lds(buf, tw, l2, lc);
+    const int64_t last = (int64_t)1 << (l1 + l2 - 1);
+    for (int q = threadIdx.x; q < n2 << lc; q += blockDim.x) {
+        const int c = q & (C - 1), k = q >> lc;
+        const int64_t bin = ((int64_t)k << l1) + c0 + c;
+        if (bin > last) continue;
+        const int j = l2 ? (int)(__brev((unsigned)k) >> (32 - l2)) : 0;
+        const double2 v = buf[fft_slot(j, c, lc)];
+        re[bin] = v.x;
+        im[bin] = v.y;
+    }
 }
 
 // Device rows to the packed host layout, written straight into pinned host
@@ -683,26 +753,33 @@ hipError_t launch_plane_fold(const float* ring, int64_t plane_nodes, const doubl
     return hipGetLastError();
 }
 
-hipError_t launch_fft(const float* series, int64_t n_samples, int n_fft, double2* a, double2* b,
-                      double2** result, hipStream_t st)
+// Bins 0 .. n_fft/2 of a probe's spectrum into re, im; a: n_fft points of scratch.
+hipError_t launch_fft(const float* series, int64_t n_samples, int n_fft, double2* a, double* re, double* im,
+                      const int32_t* bad, int32_t* bad_out, hipStream_t st)
 {
-    hipLaunchKernelGGL(fft_load, dim3((n_fft + 255) / 256), dim3(256), 0, st, series, n_samples,
-                       n_fft, a);
+    int l = 0;
+    while ((1 << l) < n_fft) ++l;
+    // columns at least as long as rows; up to 16 of them a block while they fit
+    // 4096 points (64 KiB), from 512 points on 8192 (one block per compute unit,
+    // but reads and writes of 2 points and more in a row)
+    const int l1 = (l + 1) / 2, l2 = l - l1;
+    auto block = [](int len, int count) {
+        const int cap = len >= 9 ? 13 : 12;
+        return std::min({cap - len, 4, count});
+    };
+    const int lc1 = block(l1, l2), lc2 = block(l2, l1);
+    const dim3 g1(1u << (l2 - lc1)), g2(1u << (l1 - lc2));
+    if (l1 + lc1 <= 12)
+        hipLaunchKernelGGL((fft_columns<4096>), g1, dim3(1024), 0, st, series, n_samples, l1, l2, lc1, a);
+    else
+        hipLaunchKernelGGL((fft_columns<8192>), g1, dim3(1024), 0, st, series, n_samples, l1, l2, lc1, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    double2* x = a;
-    double2* y = b;
-    for (int ns = 1; ns < n_fft; ns *= 2) {
-        hipLaunchKernelGGL(fft_pass, dim3((n_fft / 2 + 255) / 256), dim3(256), 0, st, x, y, n_fft,
-                           ns);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        double2* tmp = x;
-        x = y;
-        y = tmp;
-    }
-    *result = x;
-    return hipSuccess;
+    if (l2 + lc2 <= 12)
+        hipLaunchKernelGGL((fft_rows<4096>), g2, dim3(1024), 0, st, (const double2*)a, l1, l2, lc2, re, im, bad, bad_out);
+    else
+        hipLaunchKernelGGL((fft_rows<8192>), g2, dim3(1024), 0, st, (const double2*)a, l1, l2, lc2, re, im, bad, bad_out);
+    return hipGetLastError();
 }
 
 hipError_t launch_pack(const void* src, int elem, int64_t pitch, uint32_t len, uint32_t col, uint32_t n,

@@ -1,5 +1,5 @@
 // Fixed device scratch of the allocation-free probe spectrum
-// (fdtd_probe_fft_noalloc): the FFT's two ping-pong buffers live in a
+// (fdtd_probe_fft_noalloc): the FFT's intermediate points and its bins live in a
 // file-scope device array, so that call allocates nothing.
 //
 // The array's name is a host-side stand-in in host code, not a device address:
@@ -46,23 +46,6 @@ hipError_t noalloc_scratch(int device, void** out)
     }
     *out = g_ptr[device];
     return hipSuccess;
-}
-
-// Split bins 0..nbins-1 of a complex spectrum into re[0..nbins) and
-// im[0..nbins) of one double array (out = re, out + nbins = im).
-__global__ void fft_split(const double2* __restrict__ x, int nbins, double* __restrict__ out)
-{
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nbins) return;
-    const double2 v = x[k];
-    out[k] = v.x;
-    out[nbins + k] = v.y;
-}
-
-hipError_t launch_fft_split(const double2* x, int nbins, double* out, hipStream_t st)
-{
-    hipLaunchKernelGGL(fft_split, dim3((nbins + 255) / 256), dim3(256), 0, st, x, nbins, out);
-    return hipGetLastError();
 }
 
 }  // namespace fdtd

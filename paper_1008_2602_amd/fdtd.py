@@ -145,6 +145,12 @@ def _check(rc: int) -> int:
     return rc
 
 
+def _complex(re: np.ndarray, im: np.ndarray) -> np.ndarray:
+    out = np.empty(re.shape, np.complex128)
+    out.real, out.imag = re, im
+    return out
+
+
 def _ptr(a: Optional[np.ndarray]):
     return None if a is None else a.ctypes.data
 
@@ -266,12 +272,10 @@ def fdtd_set_plane_dft(g, k: int, f_hz: Sequence[float]):
 def fdtd_get_plane_dft(g, ny: int, nx: int) -> np.ndarray:
     """(nf, ny+1, nx+1) complex128."""
     nf = fdtd_get_info(g).plane_nf
-    re = np.zeros((nf, ny + 1, nx + 1))
-    im = np.zeros((nf, ny + 1, nx + 1))
+    re = np.empty((nf, ny + 1, nx + 1))
+    im = np.empty((nf, ny + 1, nx + 1))
     _check(_lib.fdtd_get_plane_dft(g, _ptr(re), _ptr(im)))
-    out = np.empty(re.shape, np.complex128)
-    out.real, out.imag = re, im
-    return out
+    return _complex(re, im)
 
 
 def fdtd_get_plane(g, comp: int, k: int, ny: int, nx: int) -> np.ndarray:
@@ -291,17 +295,17 @@ def fdtd_step_many(grids: Sequence, n: Sequence[int]):
 
 
 def fdtd_probe_fft(g, pid: int, n_fft: int) -> np.ndarray:
-    re = np.zeros(n_fft // 2 + 1)
-    im = np.zeros(n_fft // 2 + 1)
+    re = np.empty(n_fft // 2 + 1)
+    im = np.empty(n_fft // 2 + 1)
     _check(_lib.fdtd_probe_fft(g, int(pid), int(n_fft), _ptr(re), _ptr(im)))
-    return re + 1j * im
+    return _complex(re, im)
 
 
 def fdtd_probe_fft_noalloc(g, pid: int, n_fft: int) -> np.ndarray:
-    re = np.zeros(n_fft // 2 + 1)
-    im = np.zeros(n_fft // 2 + 1)
+    re = np.empty(n_fft // 2 + 1)
+    im = np.empty(n_fft // 2 + 1)
     _check(_lib.fdtd_probe_fft_noalloc(g, int(pid), int(n_fft), _ptr(re), _ptr(im)))
-    return re + 1j * im
+    return _complex(re, im)
 
 
 def fdtd_get_probe(g, pid: int, n: int) -> np.ndarray:
