@@ -66,6 +66,10 @@ __device__ __forceinline__ AxisCoef scale_coef(const AxisCoef& a, float w)
     return o;
 }
 
+// Which of the two E slots the front plane has (fixed in each copy of the plane's code).
+template <int N>
+struct Slot { static constexpr int value = N; };
+
 // MM: 0 the plain kernel; 1 the material variant (PML coefficients rebuilt,
 // conducting edges solved); 2 its conduction-only flavour (conducting edges
 // solved, no rebuild: tile planes whose nodes need no rebuilt coefficient).
@@ -83,28 +87,32 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
     constexpr int SC = W + 4;        // LDS columns: c = i - (i0 - 2), i0-2 .. i0+W+1
     constexpr int NT = 64 * TY + 128;
     static_assert(TY >= 5 && 4 * TY + 4 <= 64 && NT <= 1024, "tile shape");
-    __shared__ float sE0x[2][TY + 1][SC];
-    __shared__ float sE0y[2][TY + 1][SC];
-    __shared__ float sE0z[TY + 1][SC];
-    __shared__ float sH1x[TY][SC];
-    __shared__ float sH1y[TY][SC];
-    __shared__ float sH1z[TY][SC];
-    __shared__ float sE1x[2][TY][SC];
-    __shared__ float sE1y[2][TY][SC];
-    __shared__ float sE1z[2][TY][SC];
-    __shared__ float sH2x[TY][SC];
-    __shared__ float sH2y[TY][SC];
-    __shared__ float sH2z[TY][SC];
     constexpr int kLdsClasses = sizeof(CT) == 1 ? 256 : 1;
-    __shared__ ClassEntry sTab[kLdsClasses];
     // material variant: each class's 1/eps_r at the H faces and the conduction
     // of its E edges (six floats), in LDS for one-byte class indices
     constexpr int kLdsAux = MT && sizeof(CT) == 1 ? 256 : 1;
-    __shared__ float sAux[kLdsAux][6];
-    // z coefficients of plane p in slot p & 3 (planes k-1, k and k+1 are live at
-    // once), staged by the last wave; the material variant also keeps kappa
-    constexpr int NZE = RB ? 12 : 10;
-    __shared__ float sZ[4][NZE];
+    // z coefficients of plane p in slot p & (kZ - 1), filled kZ / 2 planes at a time;
+    // the material variant also keeps kappa
+    constexpr int NZE = RB ? 12 : 10, kZ = 64;
+    // planes that the column operands are loaded ahead, and the rings of E slots
+    struct Lds {
+        float E0x[2][TY + 1][SC], E0y[2][TY + 1][SC], E0z[TY + 1][SC];
+        float H1x[TY][SC], H1y[TY][SC], H1z[TY][SC];
+        float E1x[2][TY][SC], E1y[2][TY][SC], E1z[2][TY][SC];
+        float H2x[TY][SC], H2y[TY][SC], H2z[TY][SC];
+        alignas(16) float z[kZ][12];
+        ClassEntry tab[kLdsClasses];
+        float aux[kLdsAux][6];
+    };
+    __shared__ Lds lds;
+    auto &sE0x = lds.E0x, &sE0y = lds.E0y;
+    auto& sE0z = lds.E0z;
+    auto &sH1x = lds.H1x, &sH1y = lds.H1y, &sH1z = lds.H1z;
+    auto &sE1x = lds.E1x, &sE1y = lds.E1y, &sE1z = lds.E1z;
+    auto &sH2x = lds.H2x, &sH2y = lds.H2y, &sH2z = lds.H2z;
+    auto& sTab = lds.tab;
+    auto& sAux = lds.aux;
+    auto& sZ = lds.z;
 
     const TileRef t = tiles[xcd_tile(blockIdx.x, gridDim.x)];
     if (t.board < 0) return;   // idle entry padding an XCD's list
@@ -183,8 +191,7 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
     auto in_pz = [&](int k) { return (k < pml_zlo) || (pml_zhi > 0 && k >= nz - pml_zhi); };
     cgfloat* __restrict__ cxp = (cgfloat*)B.coef[0];
     cgfloat* __restrict__ cyp = (cgfloat*)B.coef[1];
-    kfloat* __restrict__ czp = (kfloat*)B.coef[2];
-    const int nx1 = nx + 1, ny1 = ny + 1, nz1 = nz + 1;
+    const int nx1 = nx + 1, ny1 = ny + 1;
     auto axis_coef = [&](cgfloat* tab, int n1, int idx) {
         const int q = min(max(idx, 0), n1 - 1);
         AxisCoef a;
@@ -204,7 +211,7 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
     };
     // z coefficients from the LDS ring (entry kind*2 + half of the table)
     auto z_coef = [&](int k) {
-        const float* z = sZ[k & 3];
+        const float* z = sZ[k & (kZ - 1)];
         AxisCoef a;
         a.cam1_n = z[kCam1 * 2 + 0];
         a.ca_n = z[kCa * 2 + 0];
@@ -216,12 +223,17 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
         a.rp_h = z[kRp * 2 + 1];
         a.ph_h = z[kPh * 2 + 1];
         a.q_h = z[kQ * 2 + 1];
-        a.k_n = RB ? z[(kKappa * 2 + 0) % NZE] : 1.0f;
-        a.k_h = RB ? z[(kKappa * 2 + 1) % NZE] : 1.0f;
+        a.k_n = RB ? z[kKappa * 2 + 0] : 1.0f;
+        a.k_h = RB ? z[kKappa * 2 + 1] : 1.0f;
         return a;
     };
-    const bool z_lane = wave == TY + 1 && lane < NZE;   // writes entry `lane` of the ring
-    const int zent = lane % NZE;
+    // fill the slots of planes p .. p + kZ/2 - 1 (read after a later barrier)
+    auto fill_z = [&](int p) {
+        for (int e = tid; e < kZ / 2 * NZE; e += NT) {
+            const int q = p + e / NZE, v = e % NZE;
+            sZ[q & (kZ - 1)][v] = ((cgfloat*)B.coef[2])[v * (nz + 1) + min(max(q, 0), nz)];
+        }
+    };
 
     if (sizeof(CT) == 1) {
         for (int e = tid; e < kLdsClasses; e += NT) {
@@ -262,30 +274,34 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
     auto at_plane = [&](int p) { return ib && (unsigned)p <= (unsigned)nz ? node0b + (uint32_t)p * szb : guardb; };
     const int64_t ms = B.max_steps;
 
-    struct Stage { float ex, ey, ez, z; };
-    struct Col { float hx, hy, hz, bx, by, bz, dx, dy, dz; CT c; };
+    struct Stage { float ex, ey, ez; };
+    struct ColH { float hx, hy, hz; };
+    struct Col { float bx, by, bz, dx, dy, dz; CT c; };
     auto load_stage = [&](int p) {
         Stage s;
         const uint32_t up = at_plane(p + 1);
         s.ex = ld_at(gE, up);
         s.ey = ld_at(gE, up + cs);
         s.ez = ld_at(gE, at_plane(p) + cs2);
-        s.z = czp[zent * nz1 + min(p, nz)];       // every lane loads one (exact wait counts)
         return s;
     };
     // Every load is issued on every path (absent operands read the zero guard
-    // words), so the wait counts stay exact.  The next plane's column operands are issued in two groups so that the
-    // vector memory pipe is not flooded at one point of the plane: H_x and H_y
-    // (read by H1) at the top of the plane; H_z, B (H1), the class and D (E1) once
-    // H1 is done; the staging loads follow the H2 phase.
-    auto load_col_h = [&](int p, Col& o) {
+    // words), so the wait counts stay exact.  The next plane's column operands are
+    // spread over the plane so that the vector memory pipe is not flooded at one
+    // point: H_x and H_y (read by H1) at the top; H_z and B once H1 is done, which
+    // has just read the registers they land in; the class and D once E1 is done,
+    // likewise; the staging loads follow the H2 phase.  Only H has two register sets:
+    // with two of all ten and the z coefficients' staging register beside them the
+    // kernel took 127 VGPRs and spilled; now 110, so nothing spills, the material
+    // variant included (16 values before).
+    auto load_col_h = [&](int p, ColH& o) {
         const uint32_t n = node0b + (uint32_t)p * szb;
         const bool okh = rH1 && ib && p <= nz;
         const uint32_t nh = okh ? n : guardb;
         o.hx = ld_at(gH, nh);
         o.hy = ld_at(gH, nh + cs);
     };
-    auto load_col_hz = [&](int p, Col& o) {
+    auto load_col_hz = [&](int p, ColH& o) {
         const uint32_t n = node0b + (uint32_t)p * szb;
         const bool okh = rH1 && ib && p <= nz;
         o.hz = ld_at(gH, (okh ? n : guardb) + cs2);
@@ -354,66 +370,57 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
         ddz = fmaf(X.cam1_n, dzo, X.rp_n * chz);
         ezn = fmaf(Y.ca_n, ezo, Y.rp_n * (ce.inv_z * fmaf(Z.ph_h, ddz, Z.q_h * dzo)));
     };
+    // The axes' coefficients of a PML node scaled for 1/eps_rw = w.  Outside its own
+    // slab an axis has q = 0, where a rebuilt coefficient is the table's bit for
+    // bit, so only the axes that are in one pay the division: one or two of
+    // three at most nodes (a face's slab or an edge's).
+    struct Scaled { AxisCoef x, y, z; };
+    auto scale_axes = [&](float w, const AxisCoef& Z, bool pzp, Scaled& o) __attribute__((always_inline)) {
+        if (px) o.x = scale_coef(X, w);
+        if (py) o.y = scale_coef(Y, w);
+        if (pzp) o.z = scale_coef(Z, w);
+    };
     // the same in a PML node of a material board: every axis's coefficients
-    // rebuilt for the face's 1/eps_rw (one at each of the Hx, Hy, Hz faces)
-    auto h_material = [&](CT id, const AxisCoef& Z, float cxe, float cye, float cze, float hxo,
+    // rebuilt for the face's 1/eps_rw (one at each of the Hx, Hy, Hz faces, which
+    // differ at a material interface only)
+    auto h_material = [&](CT id, bool pzp, const AxisCoef& Z, float cxe, float cye, float cze, float hxo,
                           float hyo, float hzo, float bxo, float byo, float bzo, float& dbx,
                           float& dby, float& dbz, float& hx, float& hy, float& hz) {
-        {
-            const float w = aux_of(id, 0);
-            const AxisCoef Ys = scale_coef(Y, w), Zs = scale_coef(Z, w), Xs = scale_coef(X, w);
-            dbx = fmaf(Ys.cam1_h, bxo, -Ys.rp_h * cxe);
-            hx = fmaf(Zs.ca_h, hxo, Zs.rp_h * fmaf(Xs.ph_n, dbx, Xs.q_n * bxo));
-        }
-        {
-            const float w = aux_of(id, 1);
-            const AxisCoef Zs = scale_coef(Z, w), Xs = scale_coef(X, w), Ys = scale_coef(Y, w);
-            dby = fmaf(Zs.cam1_h, byo, -Zs.rp_h * cye);
-            hy = fmaf(Xs.ca_h, hyo, Xs.rp_h * fmaf(Ys.ph_n, dby, Ys.q_n * byo));
-        }
-        {
-            const float w = aux_of(id, 2);
-            const AxisCoef Xs = scale_coef(X, w), Ys = scale_coef(Y, w), Zs = scale_coef(Z, w);
-            dbz = fmaf(Xs.cam1_h, bzo, -Xs.rp_h * cze);
-            hz = fmaf(Ys.ca_h, hzo, Ys.rp_h * fmaf(Zs.ph_n, dbz, Zs.q_n * bzo));
-        }
+        const float wx = aux_of(id, 0), wy = aux_of(id, 1), wz = aux_of(id, 2);
+        Scaled s{X, Y, Z};
+        scale_axes(wx, Z, pzp, s);
+        dbx = fmaf(s.y.cam1_h, bxo, -s.y.rp_h * cxe);
+        hx = fmaf(s.z.ca_h, hxo, s.z.rp_h * fmaf(s.x.ph_n, dbx, s.x.q_n * bxo));
+        if (wy != wx) scale_axes(wy, Z, pzp, s);
+        dby = fmaf(s.z.cam1_h, byo, -s.z.rp_h * cye);
+        hy = fmaf(s.x.ca_h, hyo, s.x.rp_h * fmaf(s.y.ph_n, dby, s.y.q_n * byo));
+        if (wz != wy) scale_axes(wz, Z, pzp, s);
+        dbz = fmaf(s.x.cam1_h, bzo, -s.x.rp_h * cze);
+        hz = fmaf(s.y.ca_h, hzo, s.y.rp_h * fmaf(s.z.ph_n, dbz, s.z.q_n * bzo));
     };
     // D then E of one node on a material board, in the node passes' arithmetic:
     // with `rebuild` (a PML node with some edge's 1/eps_rw != 1) every axis's
     // coefficients rebuilt for each edge's 1/eps_rw, else the table's (the same
     // bits as rebuilt at 1); an edge that conducts (lossy dielectric, resistive
     // sheet, resistive source) solved for E^{n+1} with its conduction
-    auto e_material = [&](const ClassEntry& ce, CT id, bool rebuild, int node, int64_t s,
+    auto e_material = [&](const ClassEntry& ce, CT id, bool rebuild, bool pzp, int node, int64_t s,
                           const AxisCoef& Z, float chx, float chy, float chz, float exo, float eyo,
                           float ezo, float dxo, float dyo, float dzo, float& ddx, float& ddy,
                           float& ddz, float& exn, float& eyn, float& ezn) {
         const float wx = B.eps_rw ? ce.inv_x : 1.0f, wy = B.eps_rw ? ce.inv_y : 1.0f,
                     wz = B.eps_rw ? ce.inv_z : 1.0f;
-        {
-            AxisCoef Ys = Y, Zs = Z, Xs = X;
-            if (rebuild) {
-                Ys = scale_coef(Y, wx);
-                Zs = scale_coef(Z, wx);
-                Xs = scale_coef(X, wx);
-            }
-            ddx = fmaf(Ys.cam1_n, dxo, Ys.rp_n * chx);
-            exn = fmaf(Zs.ca_n, exo, Zs.rp_n * (ce.inv_x * fmaf(Xs.ph_h, ddx, Xs.q_h * dxo)));
-        }
+        Scaled a{X, Y, Z};
+        if (rebuild) scale_axes(wx, Z, pzp, a);
+        ddx = fmaf(a.y.cam1_n, dxo, a.y.rp_n * chx);
+        exn = fmaf(a.z.ca_n, exo, a.z.rp_n * (ce.inv_x * fmaf(a.x.ph_h, ddx, a.x.q_h * dxo)));
         const float lx = aux_of(id, 3);
         if (lx != 0.0f) {
             exn = conductive_e(exo, chx, ce.inv_x, lx);
             ddx = chx - lx * (exn + exo);
         }
-        {
-            AxisCoef Zs = Z, Xs = X, Ys = Y;
-            if (rebuild) {
-                Zs = scale_coef(Z, wy);
-                Xs = scale_coef(X, wy);
-                Ys = scale_coef(Y, wy);
-            }
-            ddy = fmaf(Zs.cam1_n, dyo, Zs.rp_n * chy);
-            eyn = fmaf(Xs.ca_n, eyo, Xs.rp_n * (ce.inv_y * fmaf(Ys.ph_h, ddy, Ys.q_h * dyo)));
-        }
+        if (rebuild && wy != wx) scale_axes(wy, Z, pzp, a);
+        ddy = fmaf(a.z.cam1_n, dyo, a.z.rp_n * chy);
+        eyn = fmaf(a.x.ca_n, eyo, a.x.rp_n * (ce.inv_y * fmaf(a.y.ph_h, ddy, a.y.q_h * dyo)));
         const float ly = aux_of(id, 4);
         if (ly != 0.0f) {
             eyn = conductive_e(eyo, chy, ce.inv_y, ly);
@@ -433,16 +440,9 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
                 }
             chs -= js;
         }
-        {
-            AxisCoef Xs = X, Ys = Y, Zs = Z;
-            if (rebuild) {
-                Xs = scale_coef(X, wz);
-                Ys = scale_coef(Y, wz);
-                Zs = scale_coef(Z, wz);
-            }
-            ddz = fmaf(Xs.cam1_n, dzo, Xs.rp_n * chs);
-            ezn = fmaf(Ys.ca_n, ezo, Ys.rp_n * (ce.inv_z * fmaf(Zs.ph_h, ddz, Zs.q_h * dzo)));
-        }
+        if (rebuild && wz != wy) scale_axes(wz, Z, pzp, a);
+        ddz = fmaf(a.x.cam1_n, dzo, a.x.rp_n * chs);
+        ezn = fmaf(a.y.ca_n, ezo, a.y.rp_n * (ce.inv_z * fmaf(a.z.ph_h, ddz, a.z.q_h * dzo)));
         bs += aux_of(id, 5);   // a resistive source's lumped conductance adds to the medium's
         if (bs != 0.0f) {
             ezn = conductive_e(ezo, chs, ce.inv_z, bs);
@@ -475,14 +475,16 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
         sE0x[1][r][c] = t.ex;
         sE0y[1][r][c] = t.ey;
         sE0z[r][c] = t.ez;
-        if (z_lane) sZ[k0 & 3][lane] = t.z;
     }
     Stage s0 = load_stage(k0 + 1), s1 = load_stage(k0 + 2);
-    Col cA, cB;
-    load_col_h(k0, cA);
-    load_col_hz(k0, cA);
-    load_col_b(k0, cA);
-    load_col_cd(k0, cA);
+    ColH hA, hB;
+    Col col;
+    load_col_h(k0, hA);
+    load_col_hz(k0, hA);
+    load_col_b(k0, col);
+    load_col_cd(k0, col);
+    fill_z(k0 - 1);
+    fill_z(k0 - 1 + kZ / 2);
     __syncthreads();
 
     // carried from the previous front plane (k-1): H1, B1, own E1, D1 and class;
@@ -495,8 +497,8 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
 
     // st holds stage k+1 on entry: it is written once E1 of plane k has read plane
     // k's E^n, so the staging needs no barrier of its own (three per plane)
-    auto plane_step = [&](int k, Stage& st, const Col& o, Col& nxt_col) {
-        const int cur = (k - k0) & 1, nxt = cur ^ 1;
+    auto plane_step = [&](auto slot, int k, Stage& st, const ColH& oh, ColH& nxt_col, Col& o) __attribute__((always_inline)) {
+        constexpr int cur = decltype(slot)::value, nxt = cur ^ 1;
         const int m = k - 1;   // plane of the second step
         load_col_h(k + 1, nxt_col);
         const AxisCoef Zk = z_coef(k);
@@ -505,29 +507,32 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
         const bool okk = ib && k <= nz;
         const bool pz = in_pz(k);
         float h1x = 0.f, h1y = 0.f, h1z = 0.f, b1x = 0.f, b1y = 0.f, b1z = 0.f;
+        float exo = 0.f, eyo = 0.f, ezo = 0.f;   // the lane's own E^n of plane k
         if (rH1 && okk) {
-            const float exo = sE0x[cur][r][c], eyo = sE0y[cur][r][c], ezo = sE0z[r][c];
+            exo = sE0x[cur][r][c];
+            eyo = sE0y[cur][r][c];
+            ezo = sE0z[r][c];
             float dbx, dby, dbz;
             if constexpr (MT) {
                 const float cxe = (sE0z[r + 1][c] - ezo) * crdy - (sE0y[nxt][r][c] - eyo) * crdz;
                 const float cye = (sE0x[nxt][r][c] - exo) * crdz - (sE0z[r][c + 1] - ezo) * crdx;
                 const float cze = (sE0y[cur][r][c + 1] - eyo) * crdx - (sE0x[cur][r + 1][c] - exo) * crdy;
                 if (RB && (px || py || pz) && (class_entry(o.c).flags & kMatH))
-                    h_material(o.c, Zk, cxe, cye, cze, o.hx, o.hy, o.hz, o.bx, o.by, o.bz, dbx, dby,
+                    h_material(o.c, pz, Zk, cxe, cye, cze, oh.hx, oh.hy, oh.hz, o.bx, o.by, o.bz, dbx, dby,
                                dbz, h1x, h1y, h1z);
                 else
-                    h_plain(Zk, cxe, cye, cze, o.hx, o.hy, o.hz, o.bx, o.by, o.bz, dbx, dby, dbz, h1x,
+                    h_plain(Zk, cxe, cye, cze, oh.hx, oh.hy, oh.hz, o.bx, o.by, o.bz, dbx, dby, dbz, h1x,
                             h1y, h1z);
             } else {
                 const float cxe = (sE0z[r + 1][c] - ezo) * crdy - (sE0y[nxt][r][c] - eyo) * crdz;
                 dbx = fmaf(Y.cam1_h, o.bx, -Y.rp_h * cxe);
-                h1x = fmaf(Zk.ca_h, o.hx, Zk.rp_h * fmaf(X.ph_n, dbx, X.q_n * o.bx));
+                h1x = fmaf(Zk.ca_h, oh.hx, Zk.rp_h * fmaf(X.ph_n, dbx, X.q_n * o.bx));
                 const float cye = (sE0x[nxt][r][c] - exo) * crdz - (sE0z[r][c + 1] - ezo) * crdx;
                 dby = fmaf(Zk.cam1_h, o.by, -Zk.rp_h * cye);
-                h1y = fmaf(X.ca_h, o.hy, X.rp_h * fmaf(Y.ph_n, dby, Y.q_n * o.by));
+                h1y = fmaf(X.ca_h, oh.hy, X.rp_h * fmaf(Y.ph_n, dby, Y.q_n * o.by));
                 const float cze = (sE0y[cur][r][c + 1] - eyo) * crdx - (sE0x[cur][r + 1][c] - exo) * crdy;
                 dbz = fmaf(X.cam1_h, o.bz, -X.rp_h * cze);
-                h1z = fmaf(Y.ca_h, o.hz, Y.rp_h * fmaf(Zk.ph_n, dbz, Zk.q_n * o.bz));
+                h1z = fmaf(Y.ca_h, oh.hz, Y.rp_h * fmaf(Zk.ph_n, dbz, Zk.q_n * o.bz));
             }
             b1x = (px || py) ? o.bx + dbx : 0.f;
             b1y = (py || pz) ? o.by + dby : 0.f;
@@ -541,15 +546,13 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
         __syncthreads();
 
         load_col_hz(k + 1, nxt_col);
-        load_col_b(k + 1, nxt_col);
-        load_col_cd(k + 1, nxt_col);
+        load_col_b(k + 1, o);
         // ---- E1 of plane k: D then E, step n -> n+1
         float e1x = 0.f, e1y = 0.f, e1z = 0.f, d1x = 0.f, d1y = 0.f, d1z = 0.f;
-        const int e = cur;   // E1 plane slot of plane k (plane k-1 is in e ^ 1)
+        constexpr int e = cur, pe = cur ^ 1;   // E1 slots of planes k and k-1
         if (rE1 && okk) {
             const ClassEntry ce = class_entry(o.c);
             const int node = (int)(node0b >> 2) + k * sz;   // node index (source/probe match)
-            const float exo = sE0x[cur][r][c], eyo = sE0y[cur][r][c], ezo = sE0z[r][c];
             float ddx, ddy, ddz, exn, eyn, ezn;
             if constexpr (MT) {
                 const float chx = (h1z - sH1z[r - 1][c]) * crdy - (h1y - p_h1y) * crdz;
@@ -557,7 +560,7 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
                 const float chz = (h1y - sH1y[r][c - 1]) * crdx - (h1x - sH1x[r - 1][c]) * crdy;
                 const bool rebuild = RB && (px || py || pz) && (ce.flags & kMatE);
                 if (rebuild || (ce.flags & (kCondE | kSrcEz)))
-                    e_material(ce, o.c, rebuild, node, step, Zk, chx, chy, chz, exo, eyo, ezo, o.dx,
+                    e_material(ce, o.c, rebuild, pz, node, step, Zk, chx, chy, chz, exo, eyo, ezo, o.dx,
                                o.dy, o.dz, ddx, ddy, ddz, exn, eyn, ezn);
                 else
                     e_plain(ce, Zk, chx, chy, chz, exo, eyo, ezo, o.dx, o.dy, o.dz, ddx, ddy, ddz, exn,
@@ -583,6 +586,8 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
             if (own && k >= kb && k < ke && (ce.flags & kPrbEz)) record_probe(node, step, e1z);
             if (PL && own && k >= kb && k < ke && (ce.flags & kPlnEz)) plane_sample(0, e1z);
         }
+        const CT ck = o.c;
+        load_col_cd(k + 1, o);
         if (rE1) {
             sE1x[e][r][c] = e1x;
             sE1y[e][r][c] = e1y;
@@ -597,24 +602,23 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
         const bool pzm = in_pz(m);
         float h2x = 0.f, h2y = 0.f, h2z = 0.f;
         if (rH2 && okm) {
-            const int pe = e ^ 1;
-            const float exo = sE1x[pe][r][c], eyo = sE1y[pe][r][c], ezo = sE1z[pe][r][c];
+            const float exo = p_e1x, eyo = p_e1y, ezo = p_e1z;   // the lane's own E1 of planes m and k
             float dbx, dby, dbz;
             if constexpr (MT) {
-                const float cxe = (sE1z[pe][r + 1][c] - ezo) * crdy - (sE1y[e][r][c] - eyo) * crdz;
-                const float cye = (sE1x[e][r][c] - exo) * crdz - (sE1z[pe][r][c + 1] - ezo) * crdx;
+                const float cxe = (sE1z[pe][r + 1][c] - ezo) * crdy - (e1y - eyo) * crdz;
+                const float cye = (e1x - exo) * crdz - (sE1z[pe][r][c + 1] - ezo) * crdx;
                 const float cze = (sE1y[pe][r][c + 1] - eyo) * crdx - (sE1x[pe][r + 1][c] - exo) * crdy;
                 if (RB && (px || py || pzm) && (class_entry(p_c).flags & kMatH))
-                    h_material(p_c, Zm, cxe, cye, cze, p_h1x, p_h1y, p_h1z, p_b1x, p_b1y, p_b1z, dbx,
+                    h_material(p_c, pzm, Zm, cxe, cye, cze, p_h1x, p_h1y, p_h1z, p_b1x, p_b1y, p_b1z, dbx,
                                dby, dbz, h2x, h2y, h2z);
                 else
                     h_plain(Zm, cxe, cye, cze, p_h1x, p_h1y, p_h1z, p_b1x, p_b1y, p_b1z, dbx, dby, dbz,
                             h2x, h2y, h2z);
             } else {
-                const float cxe = (sE1z[pe][r + 1][c] - ezo) * crdy - (sE1y[e][r][c] - eyo) * crdz;
+                const float cxe = (sE1z[pe][r + 1][c] - ezo) * crdy - (e1y - eyo) * crdz;
                 dbx = fmaf(Y.cam1_h, p_b1x, -Y.rp_h * cxe);
                 h2x = fmaf(Zm.ca_h, p_h1x, Zm.rp_h * fmaf(X.ph_n, dbx, X.q_n * p_b1x));
-                const float cye = (sE1x[e][r][c] - exo) * crdz - (sE1z[pe][r][c + 1] - ezo) * crdx;
+                const float cye = (e1x - exo) * crdz - (sE1z[pe][r][c + 1] - ezo) * crdx;
                 dby = fmaf(Zm.cam1_h, p_b1y, -Zm.rp_h * cye);
                 h2y = fmaf(X.ca_h, p_h1y, X.rp_h * fmaf(Y.ph_n, dby, Y.q_n * p_b1y));
                 const float cze = (sE1y[pe][r][c + 1] - eyo) * crdx - (sE1x[pe][r + 1][c] - exo) * crdy;
@@ -640,7 +644,6 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
         sE0x[cur][r][c] = st.ex;
         sE0y[cur][r][c] = st.ey;
         sE0z[r][c] = st.ez;
-        if (z_lane) sZ[(k + 1) & 3][lane] = st.z;
         __syncthreads();
         st = load_stage(k + 3);
 
@@ -655,7 +658,7 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
                 const float chz = (h2y - sH2y[r][c - 1]) * crdx - (h2x - sH2x[r - 1][c]) * crdy;
                 const bool rebuild = RB && (px || py || pzm) && (ce.flags & kMatE);
                 if (rebuild || (ce.flags & (kCondE | kSrcEz)))
-                    e_material(ce, p_c, rebuild, node, step + 1, Zm, chx, chy, chz, p_e1x, p_e1y,
+                    e_material(ce, p_c, rebuild, pzm, node, step + 1, Zm, chx, chy, chz, p_e1x, p_e1y,
                                p_e1z, p_d1x, p_d1y, p_d1z, ddx, ddy, ddz, exn, eyn, ezn);
                 else
                     e_plain(ce, Zm, chx, chy, chz, p_e1x, p_e1y, p_e1z, p_d1x, p_d1y, p_d1z, ddx, ddy,
@@ -691,12 +694,17 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
         p_b1x = b1x; p_b1y = b1y; p_b1z = b1z;
         p_e1x = e1x; p_e1y = e1y; p_e1z = e1z;
         p_d1x = d1x; p_d1y = d1y; p_d1z = d1z;
-        p_c = o.c;
+        p_c = ck;
         p_h2x = h2x; p_h2y = h2y;
     };
+    int zfill = k0 - 1 + kZ;   // first plane not in the z ring
     for (int k = k0; k <= ke; k += 2) {
-        plane_step(k, s0, cA, cB);
-        if (k + 1 <= ke) plane_step(k + 1, s1, cB, cA);
+        if (k + kZ / 2 - 4 >= zfill) {   // the planes it takes the slots of lie below k-1
+            fill_z(zfill);
+            zfill += kZ / 2;
+        }
+        plane_step(Slot<0>{}, k, s0, hA, hB, col);
+        if (k + 1 <= ke) plane_step(Slot<1>{}, k + 1, s1, hB, hA, col);
     }
     if (bad) *(__attribute__((address_space(1))) int32_t*)B.bad = 1;
 }
