@@ -94,13 +94,14 @@ typedef struct {
     int32_t node_passes;         /* 1: steps run the node passes' arithmetic (fdtd_set_pml_eps_rw,
                                     fdtd_set_conductivity, fdtd_set_sheet_resistance) */
     int32_t material_two_step;   /* 1: of which pairs of steps run on the material two-step kernel */
-    int32_t material_permille;   /* of its tiles' node planes, the share (per mille) on the material
-                                    variant; the others run the plain two-step kernel */
+    int32_t material_permille;   /* of its tiles' node planes, the share (per mille) that needs the
+                                    material variant (on small boards whole tiles run it) */
     int32_t material_split;      /* how: 1 per tile (the variant in the plain kernel's 64 x 14 tiles),
                                     2 per plane (planes near material nodes in any tile run the
                                     64 x 10 variant for every tile), 0 no such planes */
-    int32_t conduct_permille;    /* the share (per mille) on the conduction-only flavour of the
-                                    variant (planes near conducting edges only, 64 x 14 tiles) */
+    int32_t conduct_permille;    /* the share (per mille) that needs the conduction-only flavour of
+                                    the variant (planes near conducting edges only; boards without
+                                    rebuilt planes run it on every plane) */
     int32_t batch_plans;         /* plans of fdtd_step_many calls this handle led, kept for reuse */
     int32_t batch_graphs;        /* of which captured as a graph (one graph launch per call) */
 } fdtd_info;
@@ -184,7 +185,9 @@ int fdtd_set_dft_freqs(fdtd_grid* g, const double* f_hz, int nf);
  * nodes fill those planes), whichever is estimated cheaper; planes near
  * conducting edges only run its conduction-only flavour in that tile; the
  * other planes run the plain kernel (fdtd_info.material_permille,
- * material_split, conduct_permille).  The odd last step of a call runs the node
+ * material_split, conduct_permille).  Where that is faster one kernel steps the
+ * whole board: the conduction-only flavour on boards without such PML nodes,
+ * the material variant on small ones.  The odd last step of a call runs the node
  * passes (two per-node passes, H then E).  With a one-step shape set, and on
  * boards past the tiled kernels' 4 GiB offset window, every step runs the node
  * passes.  All give the same bits.  ESTATE after the first step. */

@@ -772,6 +772,34 @@ void split_material(int nx, int ny, int nz, const std::vector<uint8_t>& tile_nee
     out.cond_permille = (int)(1000.0 * cd_tp / all);
 }
 
+// Where one kernel over whole tiles beats the split above, make its pieces the
+// whole board's tiles (every kernel gives the plain one's bits on planes that need
+// no more; the shares stay those of the planes that do).
+//  * Boards with conducting edges only: always.  Beside the field arithmetic the
+//    conduction-only flavour costs nothing (110 VGPRs, nothing spilled; 444 x 364 x 60
+//    with a lossy layer between sheets 86 us per step as the lossless board, split
+//    115-122; 1048 x 792 x 88 591, split 659), while pieces re-read their halo
+//    planes, run in two launches that crowd each other's compute units out, and
+//    join two streams every pair.
+//  * Boards with rebuilt PML coefficients: up to about 140 tile planes per compute
+//    unit.  The material variant runs whole tiles at 1.06-1.2 times the plain
+//    kernel's time (444 x 364 x 60: 101 us per step, split 118; 600 x 412 x 60: 144
+//    and 161; 800 x 500 x 60: 220 and 231), which is more than the split loses
+//    on larger boards (1000 x 700 x 60: 386 and 369; 1048 x 792 x 88: 628 and 617).
+constexpr int kMaterialWholePlanes = 140;
+void one_kernel_board(int nx, int ny, int nz, int cus, MaterialSplit& ms)
+{
+    int cx, cy;
+    tile_counts(nx, ny, 64, owned_rows(kHybridTY, 2), &cx, &cy);
+    const bool rebuilt = !ms.rb.empty();
+    if (rebuilt ? (int64_t)cx * cy * nz > (int64_t)kMaterialWholePlanes * cus : ms.cd.empty()) return;
+    ms.rb.clear();
+    ms.cd.clear();
+    ms.plain.clear();
+    board_tiles(0, nx, ny, nz, 64, owned_rows(kHybridTY, 2), rebuilt ? ms.rb : ms.cd);
+    if (rebuilt) ms.mat_ty = kHybridTY;
+}
+
 int64_t count_step_bytes(const fdtd_grid* g)
 {
     const fdtd_grid_desc& d = g->d;
@@ -1553,6 +1581,7 @@ static int upload_tiles(fdtd_grid* g)
         // nodes, and give the node passes' bits.
         MaterialSplit ms;
         split_material(g->d.nx, g->d.ny, g->d.nz, g->tile_need, ms);
+        one_kernel_board(g->d.nx, g->d.ny, g->d.nz, g->cus, ms);
         g->mat_ty = ms.mat_ty;
         g->mat_split = ms.split;
         g->mat_permille = ms.mat_permille;
