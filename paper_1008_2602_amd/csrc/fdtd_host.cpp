@@ -10,6 +10,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <numeric>
 #include <string>
 #include <unordered_map>
 #include <vector>
@@ -457,64 +458,150 @@ bool stream_stores(const fdtd_grid* const* gs, int ng)
 
 constexpr int kXcds = 8;   // the kernel deals block b to XCD b % 8 (xcd_tile)
 
+// What a block of a field launch spends besides stepping its planes, in planes: the
+// two or three planes that its z halo recomputes and the loads ahead of its first
+// plane.  From launches over 16 to 48 boards of 48 x 43 x 30 cells cut into 1 to 15
+// pieces per tile: one round of pieces costs 1.3 to 1.8 us per plane, each further
+// round 6 to 9 us more (2.5 us on boards bound by memory, 444 x 364 x 60).
+constexpr double kBlockPlanes = 4.0;
+constexpr int kMaxPieces = 16;   // of one tile in z
+
+// Pieces of at most p planes that a tile of h planes is cut into, none below two.
+int tile_pieces(int h, int p) { return std::max(1, std::min({(h + p - 1) / p, h / 2, kMaxPieces})); }
+
+// Cuts weights w (in order) into kXcds contiguous runs; end[x] is the end of run x.
+// Equal weights: at the shares' nearest boundaries, so that the runs differ by one.
+// Others: the least heaviest run there is.  Returns the heaviest run's weight.
+int split_runs(const std::vector<int>& w, size_t end[kXcds])
+{
+    const int total = std::accumulate(w.begin(), w.end(), 0);
+    auto heaviest = [&] {
+        int most = 0;
+        for (int x = 0; x < kXcds; ++x)
+            most = std::max(most, std::accumulate(w.begin() + (x ? end[x - 1] : 0), w.begin() + end[x], 0));
+        return most;
+    };
+    if (std::equal(w.begin() + 1, w.end(), w.begin())) {
+        size_t idx = 0;
+        for (int x = 0; x < kXcds; ++x) {
+            const double target = (double)total * (x + 1) / kXcds;
+            while (idx < w.size() && (x == kXcds - 1 || (idx + 0.5) * w[0] <= target)) ++idx;
+            end[x] = idx;
+        }
+        return heaviest();
+    }
+    for (int cap = std::max((total + kXcds - 1) / kXcds, *std::max_element(w.begin(), w.end()));; ++cap) {
+        size_t idx = 0;
+        for (int x = 0; x < kXcds; ++x) {
+            int sum = 0;
+            while (idx < w.size() && sum + w[idx] <= cap) sum += w[idx++];
+            end[x] = idx;
+        }
+        if (idx == w.size()) return heaviest();
+    }
+}
+
+// Tile t's piece q of n.
+TileRef piece_of(TileRef t, int q, int n)
+{
+    const int64_t planes = t.ke - t.kb;
+    t.ke = t.kb + (int)(planes * (q + 1) / n);
+    t.kb = t.kb + (int)(planes * q / n);
+    return t;
+}
+
 // Work list of one field launch.  Tiles arrive in board order, row-major within
-// a board.  They are cut into kXcds contiguous runs of about equal plane count,
-// one per XCD, so that neighbouring tiles share halos in that XCD's L2.  On each
-// XCD the tiles left over after its last full round of concurrent blocks would
-// leave most of the XCD idle in that round; they are split in z into S pieces
-// (S chosen to shorten the estimated tail, each piece after the first pays one
-// recomputed plane).  Pieces go piece-major so that concurrent pieces are
-// spatial neighbours at the same depth.  Every run is padded with idle entries
-// to the common length, so the launch has kXcds * length blocks.
+// a board.  They are cut into kXcds contiguous runs, one per XCD, so that
+// neighbouring tiles share halos in that XCD's L2, and split in z so that no
+// compute unit idles for long.
+//
+// Fewer tiles than concurrent blocks (a small board, a batch of them): all tiles
+// are cut into pieces of at most p planes, p the least that fits R rounds of
+// blocks on every XCD, R what takes least.  One p over all tiles and runs of equal
+// piece counts let tiles of different depth share the device (15 boards of 21 to
+// 91 planes: runs of equal planes, cut alike within a run, left 18 planes to the
+// longest block where 16 do).
+//
+// More: runs of about equal plane count; on each XCD the tiles left over after its
+// last full round of concurrent blocks would leave most of the XCD idle in that
+// round, and are split into S pieces (S chosen to shorten the estimated tail).
+//
+// Pieces go piece-major so that concurrent pieces are spatial neighbours at the
+// same depth.  Every run is padded with idle entries to the common length, so the
+// launch has kXcds * length blocks.
 void build_work(const std::vector<TileRef>& tiles, int slots_per_xcd, std::vector<TileRef>& out)
 {
     out.clear();
     const size_t T = tiles.size();
     if (T == 0) return;
-    double W = 0.0;
-    for (const TileRef& t : tiles) W += t.ke - t.kb;
+    const int C = std::max(1, slots_per_xcd);
     std::vector<std::vector<TileRef>> runs(kXcds);
-    size_t idx = 0;
-    double acc = 0.0;
-    for (int x = 0; x < kXcds; ++x) {
-        const double target = W * (x + 1) / kXcds;
-        std::vector<TileRef> whole;
-        while (idx < T && (x == kXcds - 1 || acc + 0.5 * (tiles[idx].ke - tiles[idx].kb) <= target)) {
-            whole.push_back(tiles[idx]);
-            acc += tiles[idx].ke - tiles[idx].kb;
-            ++idx;
+    std::vector<int> w(T), best_w;
+    int deepest = 1;
+    for (size_t q = 0; q < T; ++q) deepest = std::max(deepest, w[q] = tiles[q].ke - tiles[q].kb);
+    size_t end[kXcds];
+    if (T <= (size_t)C * kXcds) {
+        double best = HUGE_VAL;
+        std::fill(w.begin(), w.end(), 0);
+        for (int p = deepest; p >= 1; --p) {
+            int longest = 1;
+            bool cut = false;
+            for (size_t q = 0; q < T; ++q) {
+                const int h = tiles[q].ke - tiles[q].kb, n = tile_pieces(h, p);
+                cut |= n != w[q];
+                w[q] = n;
+                longest = std::max(longest, (h + n - 1) / n);
+            }
+            if (!cut) continue;
+            size_t e[kXcds];
+            const int rounds = (split_runs(w, e) + C - 1) / C;
+            if (rounds * (1 + kBlockPlanes) >= best) break;   // so are all shorter pieces
+            const double cost = rounds * (longest + kBlockPlanes);
+            if (cost < best) {
+                best = cost;
+                best_w = w;
+                std::copy(e, e + kXcds, end);
+            }
         }
-        const size_t n = whole.size(), C = (size_t)std::max(1, slots_per_xcd);
-        const size_t m = n % C;  // tiles of the partial last round
-        int S = 1;
-        if (m > 0) {
-            double pbar = 0.0;
-            for (size_t q = n - m; q < n; ++q) pbar += whole[q].ke - whole[q].kb;
-            pbar /= (double)m;
-            double best = pbar;
-            // up to 16 pieces of at least two planes: small boards (a few tiles,
-            // 30-plane columns) are latency bound, and shorter pieces cut the
-            // planes each block walks in sequence
-            for (int cand = 2; cand <= 16 && pbar / cand >= 2.0; ++cand) {
-                const double rounds = std::ceil((double)(m * cand) / (double)C);
-                const double cost = rounds * (pbar / cand + 1.0);
-                if (cost < 0.97 * best) {
-                    best = cost;
-                    S = cand;
+        for (int x = 0; x < kXcds; ++x) {
+            const size_t b = x ? end[x - 1] : 0;
+            for (int piece = 0, left = 1; left; ++piece) {
+                left = 0;
+                for (size_t q = b; q < end[x]; ++q) {
+                    if (piece < best_w[q]) runs[x].push_back(piece_of(tiles[q], piece, best_w[q]));
+                    left |= piece + 1 < best_w[q];
                 }
             }
         }
-        std::vector<TileRef>& r = runs[x];
-        r.assign(whole.begin(), whole.end() - (S > 1 ? (std::ptrdiff_t)m : 0));
-        if (S > 1)
-            for (int piece = 0; piece < S; ++piece)
-                for (size_t q = n - m; q < n; ++q) {
-                    TileRef t = whole[q];
-                    const int planes = t.ke - t.kb;
-                    t.ke = t.kb + (int)((int64_t)planes * (piece + 1) / S);
-                    t.kb = t.kb + (int)((int64_t)planes * piece / S);
-                    if (t.kb < t.ke) r.push_back(t);   // a shallow tile may give fewer pieces
+    } else {
+        const double W = std::accumulate(w.begin(), w.end(), 0.0);
+        size_t idx = 0;
+        double acc = 0.0;
+        for (int x = 0; x < kXcds; ++x) {
+            const double target = W * (x + 1) / kXcds;
+            const size_t b = idx;
+            while (idx < T && (x == kXcds - 1 || acc + 0.5 * w[idx] <= target)) acc += w[idx++];
+            const size_t m = (idx - b) % C;  // tiles of the partial last round
+            int S = 1;
+            if (m > 0) {
+                const double pbar = std::accumulate(w.begin() + (idx - m), w.begin() + idx, 0.0) / (double)m;
+                double best = pbar + kBlockPlanes;
+                for (int cand = 2; cand <= kMaxPieces && pbar / cand >= 2.0; ++cand) {
+                    const double rounds = std::ceil((double)(m * cand) / (double)C);
+                    const double cost = rounds * (std::ceil(pbar / cand) + kBlockPlanes);
+                    if (cost < best) {
+                        best = cost;
+                        S = cand;
+                    }
                 }
+            }
+            runs[x].assign(tiles.begin() + b, tiles.begin() + idx - (S > 1 ? m : 0));
+            for (int piece = 0; S > 1 && piece < S; ++piece)
+                for (size_t q = idx - m; q < idx; ++q) {
+                    const TileRef t = piece_of(tiles[q], piece, S);
+                    if (t.kb < t.ke) runs[x].push_back(t);   // a shallow tile may give fewer pieces
+                }
+        }
     }
     size_t L = 0;
     for (const auto& r : runs) L = std::max(L, r.size());
