@@ -94,7 +94,6 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
     // z coefficients of plane p in slot p & (kZ - 1), filled kZ / 2 planes at a time;
     // the material variant also keeps kappa
     constexpr int NZE = RB ? 12 : 10, kZ = 64;
-    // planes that the column operands are loaded ahead, and the rings of E slots
     struct Lds {
         float E0x[2][TY + 1][SC], E0y[2][TY + 1][SC], E0z[TY + 1][SC];
         float H1x[TY][SC], H1y[TY][SC], H1z[TY][SC];
@@ -275,51 +274,54 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
     const int64_t ms = B.max_steps;
 
     struct Stage { float ex, ey, ez; };
-    struct ColH { float hx, hy, hz; };
-    struct Col { float bx, by, bz, dx, dy, dz; CT c; };
+    struct ColH { float hx, hy, hz, bx, by, bz; };   // read by H1
+    struct ColE { float dx, dy, dz; CT c; };         // read by E1
+    const int kl = min(ke, nz);   // last front plane: of planes past it only E of the next is read
     auto load_stage = [&](int p) {
         Stage s;
-        const uint32_t up = at_plane(p + 1);
+        const uint32_t up = p <= kl ? at_plane(p + 1) : guardb;
         s.ex = ld_at(gE, up);
         s.ey = ld_at(gE, up + cs);
-        s.ez = ld_at(gE, at_plane(p) + cs2);
+        s.ez = ld_at(gE, (p <= kl ? at_plane(p) : guardb) + cs2);
         return s;
     };
     // Every load is issued on every path (absent operands read the zero guard
-    // words), so the wait counts stay exact.  The next plane's column operands are
-    // spread over the plane so that the vector memory pipe is not flooded at one
-    // point: H_x and H_y (read by H1) at the top; H_z and B once H1 is done, which
-    // has just read the registers they land in; the class and D once E1 is done,
-    // likewise; the staging loads follow the H2 phase.  Only H has two register sets:
-    // with two of all ten and the z coefficients' staging register beside them the
-    // kernel took 127 VGPRs and spilled; now 110, so nothing spills, the material
-    // variant included (16 values before).
+    // words), so the wait counts stay exact.  A column operand is loaded two planes
+    // ahead, into the registers of the plane in hand as soon as these have been read
+    // for the last time, so two register sets carry one and a half planes of loads
+    // in flight: H_x and H_y straight after H1, H_z and B behind its barrier, the
+    // class and D after E1; the staging loads follow the staged values' LDS writes.
+    // One plane ahead, with H alone in two sets (110 VGPRs, now 117), the loads of a
+    // plane stood in the memory pipe behind the stores of the one before and came
+    // late: 1048 x 792 x 88 584 -> 542 us per step, 444 x 364 x 60 86.1 -> 82.4,
+    // 600 x 500 x 24 67.0 -> 62.3.  Where in the plane they go matters as much: H in
+    // the E2 phase 625, everything before the first barrier 552, B after E1 556.
     auto load_col_h = [&](int p, ColH& o) {
         const uint32_t n = node0b + (uint32_t)p * szb;
-        const bool okh = rH1 && ib && p <= nz;
+        const bool okh = rH1 && ib && p <= kl;
         const uint32_t nh = okh ? n : guardb;
         o.hx = ld_at(gH, nh);
         o.hy = ld_at(gH, nh + cs);
     };
     auto load_col_hz = [&](int p, ColH& o) {
         const uint32_t n = node0b + (uint32_t)p * szb;
-        const bool okh = rH1 && ib && p <= nz;
+        const bool okh = rH1 && ib && p <= kl;
         o.hz = ld_at(gH, (okh ? n : guardb) + cs2);
     };
-    auto load_col_b = [&](int p, Col& o) {
+    auto load_col_b = [&](int p, ColH& o) {
         const uint32_t n = node0b + (uint32_t)p * szb;
         const bool pz = in_pz(p);
-        const bool okh = rH1 && ib && p <= nz;
+        const bool okh = rH1 && ib && p <= kl;
         o.bx = ld_at(gB, okh && (px || py) ? n : guardb);
         o.by = ld_at(gB, (okh && (py || pz) ? n : guardb) + cs);
         o.bz = ld_at(gB, (okh && (pz || px) ? n : guardb) + cs2);
     };
-    auto load_col_cd = [&](int p, Col& o) {
+    auto load_col_cd = [&](int p, ColE& o) {
         const uint32_t n = node0b + (uint32_t)p * szb;
         const bool pz = in_pz(p);
-        const bool oke = rE1 && ib && p <= nz;
+        const bool oke = rE1 && ib && p <= kl;
         // the material variant's H1 needs the class on every H1 lane
-        const uint32_t ne = (RB ? rH1 && ib && p <= nz : oke) ? n : guardb;
+        const uint32_t ne = (RB ? rH1 && ib && p <= kl : oke) ? n : guardb;
         o.c = ld_at_t<CT>(cls, sizeof(CT) == 1 ? ne >> 2 : ne >> 1);
         o.dx = ld_at(gD, oke && (px || py) ? n : guardb);
         o.dy = ld_at(gD, (oke && (py || pz) ? n : guardb) + cs);
@@ -465,6 +467,8 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
         st_at<SS>(B.plane_ring, (uint32_t)(now & (kPlaneRing - 1)) * szb + node0b, ez);
     };
 
+    fill_z(k0 - 1);
+    fill_z(k0 - 1 + kZ / 2);
     // staging of the first front plane: E_x, E_y of planes k0 (slot 0) and k0+1
     // (slot 1), E_z of plane k0.  Stage p (E_x, E_y of plane p+1, E_z of plane p)
     // is loaded two front planes before it is written.
@@ -478,13 +482,15 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
     }
     Stage s0 = load_stage(k0 + 1), s1 = load_stage(k0 + 2);
     ColH hA, hB;
-    Col col;
+    ColE cA, cB;
     load_col_h(k0, hA);
     load_col_hz(k0, hA);
-    load_col_b(k0, col);
-    load_col_cd(k0, col);
-    fill_z(k0 - 1);
-    fill_z(k0 - 1 + kZ / 2);
+    load_col_h(k0 + 1, hB);
+    load_col_hz(k0 + 1, hB);
+    load_col_b(k0, hA);
+    load_col_b(k0 + 1, hB);
+    load_col_cd(k0, cA);
+    load_col_cd(k0 + 1, cB);
     __syncthreads();
 
     // carried from the previous front plane (k-1): H1, B1, own E1, D1 and class;
@@ -497,10 +503,9 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
 
     // st holds stage k+1 on entry: it is written once E1 of plane k has read plane
     // k's E^n, so the staging needs no barrier of its own (three per plane)
-    auto plane_step = [&](auto slot, int k, Stage& st, const ColH& oh, ColH& nxt_col, Col& o) __attribute__((always_inline)) {
+    auto plane_step = [&](auto slot, int k, Stage& st, ColH& oh, ColE& o) __attribute__((always_inline)) {
         constexpr int cur = decltype(slot)::value, nxt = cur ^ 1;
         const int m = k - 1;   // plane of the second step
-        load_col_h(k + 1, nxt_col);
         const AxisCoef Zk = z_coef(k);
 
         // ---- H1 of plane k: B then H, step n -> n+1/2
@@ -518,26 +523,27 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
                 const float cye = (sE0x[nxt][r][c] - exo) * crdz - (sE0z[r][c + 1] - ezo) * crdx;
                 const float cze = (sE0y[cur][r][c + 1] - eyo) * crdx - (sE0x[cur][r + 1][c] - exo) * crdy;
                 if (RB && (px || py || pz) && (class_entry(o.c).flags & kMatH))
-                    h_material(o.c, pz, Zk, cxe, cye, cze, oh.hx, oh.hy, oh.hz, o.bx, o.by, o.bz, dbx, dby,
+                    h_material(o.c, pz, Zk, cxe, cye, cze, oh.hx, oh.hy, oh.hz, oh.bx, oh.by, oh.bz, dbx, dby,
                                dbz, h1x, h1y, h1z);
                 else
-                    h_plain(Zk, cxe, cye, cze, oh.hx, oh.hy, oh.hz, o.bx, o.by, o.bz, dbx, dby, dbz, h1x,
+                    h_plain(Zk, cxe, cye, cze, oh.hx, oh.hy, oh.hz, oh.bx, oh.by, oh.bz, dbx, dby, dbz, h1x,
                             h1y, h1z);
             } else {
                 const float cxe = (sE0z[r + 1][c] - ezo) * crdy - (sE0y[nxt][r][c] - eyo) * crdz;
-                dbx = fmaf(Y.cam1_h, o.bx, -Y.rp_h * cxe);
-                h1x = fmaf(Zk.ca_h, oh.hx, Zk.rp_h * fmaf(X.ph_n, dbx, X.q_n * o.bx));
+                dbx = fmaf(Y.cam1_h, oh.bx, -Y.rp_h * cxe);
+                h1x = fmaf(Zk.ca_h, oh.hx, Zk.rp_h * fmaf(X.ph_n, dbx, X.q_n * oh.bx));
                 const float cye = (sE0x[nxt][r][c] - exo) * crdz - (sE0z[r][c + 1] - ezo) * crdx;
-                dby = fmaf(Zk.cam1_h, o.by, -Zk.rp_h * cye);
-                h1y = fmaf(X.ca_h, oh.hy, X.rp_h * fmaf(Y.ph_n, dby, Y.q_n * o.by));
+                dby = fmaf(Zk.cam1_h, oh.by, -Zk.rp_h * cye);
+                h1y = fmaf(X.ca_h, oh.hy, X.rp_h * fmaf(Y.ph_n, dby, Y.q_n * oh.by));
                 const float cze = (sE0y[cur][r][c + 1] - eyo) * crdx - (sE0x[cur][r + 1][c] - exo) * crdy;
-                dbz = fmaf(X.cam1_h, o.bz, -X.rp_h * cze);
-                h1z = fmaf(Y.ca_h, oh.hz, Y.rp_h * fmaf(Zk.ph_n, dbz, Zk.q_n * o.bz));
+                dbz = fmaf(X.cam1_h, oh.bz, -X.rp_h * cze);
+                h1z = fmaf(Y.ca_h, oh.hz, Y.rp_h * fmaf(Zk.ph_n, dbz, Zk.q_n * oh.bz));
             }
-            b1x = (px || py) ? o.bx + dbx : 0.f;
-            b1y = (py || pz) ? o.by + dby : 0.f;
-            b1z = (pz || px) ? o.bz + dbz : 0.f;
+            b1x = (px || py) ? oh.bx + dbx : 0.f;
+            b1y = (py || pz) ? oh.by + dby : 0.f;
+            b1z = (pz || px) ? oh.bz + dbz : 0.f;
         }
+        load_col_h(k + 2, oh);
         if (rH1) {
             sH1x[r][c] = h1x;
             sH1y[r][c] = h1y;
@@ -545,8 +551,8 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
         }
         __syncthreads();
 
-        load_col_hz(k + 1, nxt_col);
-        load_col_b(k + 1, o);
+        load_col_hz(k + 2, oh);
+        load_col_b(k + 2, oh);
         // ---- E1 of plane k: D then E, step n -> n+1
         float e1x = 0.f, e1y = 0.f, e1z = 0.f, d1x = 0.f, d1y = 0.f, d1z = 0.f;
         constexpr int e = cur, pe = cur ^ 1;   // E1 slots of planes k and k-1
@@ -587,7 +593,7 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
             if (PL && own && k >= kb && k < ke && (ce.flags & kPlnEz)) plane_sample(0, e1z);
         }
         const CT ck = o.c;
-        load_col_cd(k + 1, o);
+        load_col_cd(k + 2, o);
         if (rE1) {
             sE1x[e][r][c] = e1x;
             sE1y[e][r][c] = e1y;
@@ -644,8 +650,8 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
         sE0x[cur][r][c] = st.ex;
         sE0y[cur][r][c] = st.ey;
         sE0z[r][c] = st.ez;
-        __syncthreads();
         st = load_stage(k + 3);
+        __syncthreads();
 
         // ---- E2 of plane m on the owned patch: D then E, step n+1 -> n+2
         if (own && livem) {
@@ -703,8 +709,8 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
             fill_z(zfill);
             zfill += kZ / 2;
         }
-        plane_step(Slot<0>{}, k, s0, hA, hB, col);
-        if (k + 1 <= ke) plane_step(Slot<1>{}, k + 1, s1, hB, hA, col);
+        plane_step(Slot<0>{}, k, s0, hA, cA);
+        if (k + 1 <= ke) plane_step(Slot<1>{}, k + 1, s1, hB, cB);
     }
     if (bad) *(__attribute__((address_space(1))) int32_t*)B.bad = 1;
 }
@@ -713,11 +719,11 @@ __attribute__((amdgpu_waves_per_eu(TY <= 6 ? 4 : 1))) void field_step2(const Boa
 struct Shape2 {
     int tx, ty;
 };
-// 64*TY + 128 threads.  TY = 14 and 12 run four waves per SIMD (128 VGPRs, two
-// values spilled, four in the plane-DFT variant); 10, 9 and 8 run three (the
-// kernel's 129-131 VGPRs fit); TY = 6 is held to 128 VGPRs so that two of its
-// 512-thread blocks share a compute unit.  Taller tiles recompute fewer halo rows
-// per owned row.
+// 64*TY + 128 threads.  All shapes fit 120 VGPRs, four waves per SIMD, without
+// spilling (116-117, 119 in the plane-DFT variant): TY = 14 fills a compute unit
+// with one block, two 512-thread blocks of TY = 6 share one, and between them one
+// block leaves wave slots idle.  Taller tiles recompute fewer halo rows per owned
+// row.
 static const Shape2 kShapes2[] = {{64, 14}, {64, 12}, {64, 10}, {64, 9}, {64, 8}, {64, 6}};
 static const int kNumShapes2 = sizeof(kShapes2) / sizeof(kShapes2[0]);
 
@@ -802,12 +808,13 @@ hipError_t launch_field_step2(int tile_y, const BoardDev* boards, const TileRef*
 }
 
 // The material variant (Eq. 2's eps_rw in a dielectric PML, conduction), in two
-// shapes.  64 x kHybridTY x 2 shares the plain kernel's tiles on a material
-// board (which runs each tile's planes near material nodes on it and the rest
-// on the plain kernel); at 128 VGPRs it spills about 15 values.  64 x kMatTY x 2,
-// whose three waves per SIMD leave it the registers it needs, takes planes where
-// such nodes fill the board.  The conduction-only flavour (no rebuilt coefficients)
-// fits 64 x kHybridTY x 2 in 128 VGPRs without spilling.
+// shapes.  64 x kHybridTY x 2 shares the plain kernel's tiles on a material board,
+// whole tiles or those planes of a tile that are near material nodes, at 128 VGPRs
+// with seven values spilled (with its operands one plane ahead it spilled two and
+// took 3 to 7 % longer: 600 x 412 x 60 143.5 us per step, now 139).  64 x kMatTY x 2, whose
+// three waves per SIMD leave it the registers it needs, takes planes where such nodes
+// fill the board.  The conduction-only flavour (no rebuilt coefficients) fits
+// 64 x kHybridTY x 2 in 114 VGPRs without spilling.
 template <int TY, int MM>
 static int mat_occupancy(bool wide)
 {
