@@ -781,9 +781,10 @@ struct MaterialSplit {
 // conducting edges its conduction-only flavour (which fits the hybrid shape
 // without spilling); the rest the plain kernel.  Runs of one kind in a tile
 // are one piece.  The material variant's planes are split one of two ways, the
-// cheaper by the measured cost of a tile plane on each kernel (large board, per
-// step: plain 64 x 14 0.615 ms, material 64 x 14 1.00 ms, material 64 x 10
-// 0.82 ms):
+// cheaper by the cost of a tile plane on each kernel where every node is rebuilt
+// (large board, per step: plain 64 x 14 0.615 ms, material 64 x 14 1.00 ms, material
+// 64 x 10 0.82 ms, measured before the kernels' registers were cut; with a slab's PML
+// nodes rebuilt alone whole tiles now take 0.542 and 0.59 ms):
 //  * per tile: each tile's planes near such nodes on the variant in the plain
 //    kernel's tiles (where it spills), best when few tiles hold them (a board
 //    running into the PML with eps_rw);
@@ -863,17 +864,18 @@ void split_material(int nx, int ny, int nz, const std::vector<uint8_t>& tile_nee
 // whole board's tiles (every kernel gives the plain one's bits on planes that need
 // no more; the shares stay those of the planes that do).
 //  * Boards with conducting edges only: always.  Beside the field arithmetic the
-//    conduction-only flavour costs nothing (110 VGPRs, nothing spilled; 444 x 364 x 60
-//    with a lossy layer between sheets 86 us per step as the lossless board, split
-//    115-122; 1048 x 792 x 88 591, split 659), while pieces re-read their halo
-//    planes, run in two launches that crowd each other's compute units out, and
-//    join two streams every pair.
-//  * Boards with rebuilt PML coefficients: up to about 140 tile planes per compute
-//    unit.  The material variant runs whole tiles at 1.06-1.2 times the plain
-//    kernel's time (444 x 364 x 60: 101 us per step, split 118; 600 x 412 x 60: 144
-//    and 161; 800 x 500 x 60: 220 and 231), which is more than the split loses
-//    on larger boards (1000 x 700 x 60: 386 and 369; 1048 x 792 x 88: 628 and 617).
-constexpr int kMaterialWholePlanes = 140;
+//    conduction-only flavour costs nothing (114 VGPRs, nothing spilled; 444 x 364 x 60
+//    with a lossy layer between sheets 82 us per step as the lossless board, 1048 x
+//    792 x 88 552; split 115-122 and 659 before either kernel was sped up), while
+//    pieces re-read their halo planes, run in two launches that crowd each other's
+//    compute units out, and join two streams every pair.
+//  * Boards with rebuilt PML coefficients: up to about 200 tile planes per compute
+//    unit.  The material variant runs whole tiles at 1.06-1.15 times the plain
+//    kernel's time (us per step, whole and split: 444 x 364 x 60 95 and 104; 600 x
+//    412 x 60 139 and 163; 800 x 500 x 60 208 and 220; 900 x 600 x 60, 193 planes,
+//    277 and 297), which is more than the split loses on larger boards (1000 x 700 x
+//    60, 240 planes, 372 and 335; 1048 x 792 x 88 591 and 577).
+constexpr int kMaterialWholePlanes = 200;
 void one_kernel_board(int nx, int ny, int nz, int cus, MaterialSplit& ms)
 {
     int cx, cy;

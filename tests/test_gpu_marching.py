@@ -59,8 +59,8 @@ def test_deep_columns_refill_the_z_coefficients(F, nz, tile):
         assert np.array_equal(x, y), q
 
 
-# about 140 tile planes per compute unit (of 256): 260 tiles of 137 planes and of 139
-@pytest.mark.parametrize("nz", [137, 139])
+# about 200 tile planes per compute unit (of 256): 260 tiles of 196 planes and of 197
+@pytest.mark.parametrize("nz", [196, 197])
 @pytest.mark.parametrize("lossy", [False, True], ids=["eps_rw", "eps_rw+lossy"])
 def test_material_boards_either_side_of_the_whole_tile_rule(F, nz, lossy):
     print(f"[gpu] material rule nz={nz} lossy={lossy}", flush=True)
