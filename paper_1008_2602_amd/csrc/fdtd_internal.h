@@ -32,13 +32,13 @@ constexpr int kGraphChunk = 32;
 constexpr int kPlaneRing = 32;
 static_assert(kGraphChunk == kPlaneRing, "a graph chunk fills the ring exactly once");
 
-// largest transform of the allocation-free probe spectrum: its two FP64 complex
-// ping-pong buffers (32 B per point, 32 MiB) sit in a fixed device array
+// largest transform of the allocation-free probe spectrum: its FP64 complex points
+// and its bins (32 B per point, 32 MiB) sit in a fixed device array
 constexpr int kNoAllocFftMax = 1 << 20;
 
-// tile rows of the two-step kernel's material variant (64 x kMatTY x 2), and of
-// the plain two-step pieces that step a material board's planes clear of
-// material nodes (64 x kHybridTY x 2)
+// tile rows of the two-step kernel's material variant where it takes whole node
+// planes (64 x kMatTY x 2), and of every other two-step kernel of a material board:
+// whole tiles or pieces, plain, conduction-only or material (64 x kHybridTY x 2)
 constexpr int kMatTY = 10;
 constexpr int kHybridTY = 14;
 
