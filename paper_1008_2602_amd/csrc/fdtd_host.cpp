@@ -446,7 +446,8 @@ hipError_t launch_pass(int tx, int ty, int steps, const BoardDev* boards, const 
 // is still reading, which non-temporal stores keep (the large board: 0.618 ->
 // 0.597 ms per step); boards whose fields fit in the Infinity Cache find
 // them there at the next launch with ordinary stores (the z-convergence batch,
-// about 100 MB: 7 % slower with non-temporal stores).  The measure is the
+// 131 MB: 59 us per pair, 65 with non-temporal stores; batches of 48 x 43 x 30
+// boards: 120 MB 47 and 59, 200 MB 88 and 89, 240 MB 121 and 100).  The measure is the
 // library's fused step count (one read and one write of every kept array).
 constexpr int64_t kStreamStoreBytes = 192ll << 20;
 bool stream_stores(const fdtd_grid* const* gs, int ng)
