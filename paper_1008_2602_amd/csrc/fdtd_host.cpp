@@ -219,6 +219,7 @@ struct fdtd_grid {
     bool tile_set = false;  // by fdtd_set_tile
     int brick = -1;         // >= 0: pairs of steps run the small-board kernel in this brick shape
     int par0 = 0;           // field copy at the start of the launches being enqueued (bricks)
+    bool recorded = false;  // the caller is recording the call being enqueued into a graph of its own
     int cus = 0;            // compute units of the device
     int64_t step_bytes = 0;
 
@@ -1816,7 +1817,7 @@ static int enqueue_launch(fdtd_grid* g, bool single, int rel, int flip)
         if (int e = record_event(g)) return e;
     if (g->mat)
         HIP_OR_FAIL(single ? node_step(g, rel, flip, g->stream) : material_pair(g, rel, flip, g->stream));
-    else if (!single && g->brick >= 0)
+    else if (!single && g->brick >= 0 && !g->recorded)
         HIP_OR_FAIL(launch_brick(g->brick, g->board_host, (g->par0 + flip) & 1, rel, g->wide,
                                  g->plane_k >= 0, g->stream));
     else if (single && g->tile_steps == 2)
@@ -1897,6 +1898,20 @@ static void build_graph(fdtd_grid* g)
     (void)hipGetLastError();
 }
 
+// Whether the caller is recording the stream into a graph.  A brick launch is told
+// which field copy to read, so a recorded one would read the same copy at every
+// replay; recorded pairs of steps run the marching kernel, which takes the copy from
+// the device counters that the recorded advance moves on.
+static bool stream_recorded(hipStream_t st)
+{
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &s) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return s != hipStreamCaptureStatusNone;
+}
+
 int fdtd_step_n(fdtd_grid* g, int64_t n)
 {
     if (int e = check_grid(g)) return e;
@@ -1929,7 +1944,8 @@ int fdtd_step_n(fdtd_grid* g, int64_t n)
     // host's time, so short calls of such boards go without.
     const int64_t first = g->brick >= 0 ? 32 * kGraphChunk : kGraphChunk;
     const bool have = g->graph_exec[g->brick >= 0 ? g->buf : 0] != nullptr;
-    const bool graph = !g->timing && n >= kGraphChunk && (have || g->brick < 0 || n >= 2 * first);
+    g->recorded = g->brick >= 0 && stream_recorded(g->stream);
+    const bool graph = !g->timing && !g->recorded && n >= kGraphChunk && (have || g->brick < 0 || n >= 2 * first);
     if (graph && !have && n >= 2 * first)
         if (int e = plain(first)) return e;
     if (graph) {
