@@ -10,6 +10,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <numeric>
 #include <string>
 #include <unordered_map>
@@ -238,7 +239,7 @@ struct fdtd_grid {
     // pinned host memory that results pass through on their way to the caller: one
     // line holding the watchdog flag, then two halves filled in turn (read_out)
     char* pin = nullptr;
-    size_t pin_half = 0;
+    size_t pin_half = 0, pin_room = 0;   // bytes of a half used, and there are
     hipEvent_t pin_ev[2] = {nullptr, nullptr};
 
     // batched calls led by this handle: their plans (tables in device memory and
@@ -319,9 +320,68 @@ struct Piece {
     void* out;
 };
 
+// Pinned buffers outlive their handles: hipHostFree, like hipFree, waits for all work
+// on the device, but a handle whose device memory comes from the caller's allocator
+// is released without that wait (a server releases finished boards while others
+// step; freeing the buffer made it 164 ms behind 2000 steps of a 444 x 364 x 60
+// board, 0.07 ms without).  A released buffer is kept for the next handle of its
+// device and size, up to kPinsKept of them and kPinsKeptBytes.  They are freed when
+// the last handle goes, unless its release would wait for nothing else.
+constexpr int kPinsKept = 256;
+constexpr size_t kPinsKeptBytes = 256u << 20;
+struct PinPool {
+    struct Kept {
+        char* p;
+        size_t room;
+        int device;
+    };
+    std::mutex lock;
+    Kept kept[kPinsKept];
+    int n = 0, handles = 0;
+    size_t bytes = 0;   // of the kept buffers' halves
+};
+PinPool g_pins;
+
+char* take_pin(int device, size_t room)
+{
+    std::lock_guard<std::mutex> hold(g_pins.lock);
+    ++g_pins.handles;
+    for (int q = g_pins.n - 1; q >= 0; --q)
+        if (g_pins.kept[q].device == device && g_pins.kept[q].room == room) {
+            char* p = g_pins.kept[q].p;
+            g_pins.kept[q] = g_pins.kept[--g_pins.n];
+            g_pins.bytes -= 2 * room;
+            return p;
+        }
+    return nullptr;
+}
+
+// p may be null (the handle never got its buffer); waits: the release frees device
+// memory with hipFree.  Nothing on the device uses the buffer any more.
+void give_pin(int device, size_t room, char* p, bool waits)
+{
+    PinPool::Kept out[kPinsKept + 1];
+    int n = 0;
+    {
+        std::lock_guard<std::mutex> hold(g_pins.lock);
+        --g_pins.handles;
+        if (p && g_pins.n < kPinsKept && g_pins.bytes + 2 * room <= kPinsKeptBytes) {
+            g_pins.kept[g_pins.n++] = PinPool::Kept{p, room, device};
+            g_pins.bytes += 2 * room;
+        } else if (p) {
+            out[n++] = PinPool::Kept{p, room, device};
+        }
+        if (g_pins.handles == 0 && waits) {
+            while (g_pins.n > 0) out[n++] = g_pins.kept[--g_pins.n];
+            g_pins.bytes = 0;
+        }
+    }
+    while (n > 0) (void)hipHostFree(out[--n].p);
+}
+
 // The pinned buffer's halves hold a node plane, within these bounds; longer
 // results pass through in turns.  It is made with the handle, so that no getter
-// allocates: 2 MiB takes about 60 us over the host link and 512 KiB about 20 us,
+// pins memory: 2 MiB takes about 60 us over the host link and 512 KiB about 20 us,
 // both above the cost of a launch and a wait, and 1 MiB of pinned memory takes
 // 10-40 us to allocate.
 constexpr size_t kPinHalfMin = 512u << 10, kPinHalfMax = 2u << 20, kPinHead = 256;
@@ -329,7 +389,15 @@ hipError_t make_pin(fdtd_grid* g)
 {
     const size_t plane = (size_t)g->pitch * (g->d.ny + 1) * 4;
     g->pin_half = (std::min(std::max(plane, kPinHalfMin), kPinHalfMax) + 255) & ~size_t(255);
-    hipError_t e = hipHostMalloc((void**)&g->pin, kPinHead + 2 * g->pin_half, hipHostMallocDefault);
+    g->pin_room = kPinHalfMin;   // of three sizes, so that boards of different planes share them
+    while (g->pin_room < g->pin_half) g->pin_room *= 2;
+    g->pin = take_pin(g->device, g->pin_room);
+    hipError_t e = hipSuccess;
+    if (!g->pin) e = hipHostMalloc((void**)&g->pin, kPinHead + 2 * g->pin_room, hipHostMallocDefault);
+    if (e != hipSuccess) {
+        g->pin = nullptr;
+        give_pin(g->device, g->pin_room, nullptr, false);
+    }
     for (int h = 0; h < 2 && e == hipSuccess; ++h)
         e = hipEventCreateWithFlags(&g->pin_ev[h], hipEventDisableTiming);
     return e;
@@ -2853,7 +2921,7 @@ int fdtd_destroy_grid(fdtd_grid* g)
     if (!g) return FDTD_OK;
     if (g->stream) (void)hipStreamSynchronize(g->stream);
     for (hipEvent_t e : g->ev_pool) (void)hipEventDestroy(e);
-    if (g->pin) (void)hipHostFree(g->pin);
+    if (g->pin) give_pin(g->device, g->pin_room, g->pin, !g->d.dev_free);
     for (hipEvent_t e : g->pin_ev)
         if (e) (void)hipEventDestroy(e);
     for (hipGraphExec_t e : g->graph_exec)
