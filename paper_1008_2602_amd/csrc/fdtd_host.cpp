@@ -403,63 +403,70 @@ hipError_t make_pin(fdtd_grid* g)
     return e;
 }
 
+// Where a read-out stands: element `done` of piece `q`.
+struct Cursor {
+    int q;
+    int64_t done;
+};
+
+// Lay out what one pinned half of `room` bytes holds of the pieces from `c` on:
+// run(piece, first element, elements, byte in the half), a code, for each stretch.
+// Returns where the next half starts in `c`.
+template <class Run>
+int fill_half(const Piece* pc, int npc, size_t room, Cursor& c, Run run)
+{
+    for (size_t used = 0; c.q < npc;) {
+        const Piece& p = pc[c.q];
+        const int64_t n = p.rows * p.len;
+        const int64_t take = std::min(n - c.done, (int64_t)((room - used) / p.elem));
+        if (n > c.done && take <= 0) return FDTD_OK;
+        if (take > 0)
+            if (int e = run(p, c.done, take, used)) return e;
+        used = std::min((used + (size_t)take * p.elem + 15) & ~size_t(15), room);
+        c.done += take;
+        if (c.done < n) return FDTD_OK;
+        c = Cursor{c.q + 1, 0};
+    }
+    return FDTD_OK;
+}
+
 // Bring results to the host after the work queued on the handle's stream, which
 // has finished when this returns.  The device packs the pieces into one pinned
 // half while the host copies the other one out.  With `bad`, also the watchdog
-// flag as it is then.
+// flag as it is then.  Allocates nothing.
 int read_out(fdtd_grid* g, const Piece* pc, int npc, int32_t* bad = nullptr)
 {
-    struct Part {
-        char* to;
-        const char* from;
-        size_t bytes;
-    };
-    std::vector<Part> parts[2];
-    int q = 0;
-    int64_t done = 0;   // elements of piece q already queued
-    bool first = true;
-    int half = 0;
+    Cursor at{0, 0}, from[2];
+    bool queued[2] = {false, false}, first = true;
     auto drain = [&](int h) -> int {
-        if (parts[h].empty()) return FDTD_OK;
+        if (!queued[h]) return FDTD_OK;
+        queued[h] = false;
         HIP_OR_FAIL(hipEventSynchronize(g->pin_ev[h]));
-        for (const Part& p : parts[h]) memcpy(p.to, p.from, p.bytes);
-        parts[h].clear();
-        return FDTD_OK;
+        const char* base = g->pin + kPinHead + h * g->pin_half;
+        return fill_half(pc, npc, g->pin_half, from[h], [&](const Piece& p, int64_t done, int64_t take, size_t used) {
+            memcpy((char*)p.out + done * p.elem, base + used, (size_t)take * p.elem);
+            return FDTD_OK;
+        });
     };
-    while (q < npc) {
-        char* base = g->pin + kPinHead + half * g->pin_half;
-        size_t used = 0;
-        while (q < npc) {
-            const Piece& p = pc[q];
-            const int64_t n = p.rows * p.len, left = n - done;
-            const int64_t fit = (int64_t)((g->pin_half - used) / p.elem);
-            const int64_t take = std::min(left, fit);
-            if (left > 0 && take <= 0) break;
-            if (take > 0) {
-                const int64_t r0 = done / p.len, col = done % p.len;
-                const bool flat = p.rows == 1 || p.pitch == p.len;
-                const char* src = (const char*)p.src + (flat ? done : r0 * p.pitch) * p.elem;
-                HIP_OR_FAIL(launch_pack(src, p.elem, flat ? take : p.pitch,
-                                        (uint32_t)(flat ? take : p.len), flat ? 0u : (uint32_t)col,
-                                        (uint32_t)take, p.scale, base + used,
-                                        bad && first ? g->bad_dev : nullptr,
-                                        bad && first ? (int32_t*)g->pin : nullptr, g->stream));
-                first = false;
-                parts[half].push_back(Part{(char*)p.out + done * p.elem, base + used, (size_t)take * p.elem});
-                used += ((size_t)take * p.elem + 15) & ~size_t(15);
-                used = std::min(used, g->pin_half);
-                done += take;
-            }
-            if (done == n) {
-                ++q;
-                done = 0;
-            } else {
-                break;
-            }
-        }
-        HIP_OR_FAIL(hipEventRecord(g->pin_ev[half], g->stream));
-        half ^= 1;
+    int half = 0;
+    for (; at.q < npc; half ^= 1) {
         if (int e = drain(half)) return e;
+        char* base = g->pin + kPinHead + half * g->pin_half;
+        from[half] = at;
+        const int e = fill_half(pc, npc, g->pin_half, at, [&](const Piece& p, int64_t done, int64_t take, size_t used) {
+            const int64_t r0 = done / p.len, col = done % p.len;
+            const bool flat = p.rows == 1 || p.pitch == p.len;
+            const char* src = (const char*)p.src + (flat ? done : r0 * p.pitch) * p.elem;
+            HIP_OR_FAIL(launch_pack(src, p.elem, flat ? take : p.pitch, (uint32_t)(flat ? take : p.len),
+                                    flat ? 0u : (uint32_t)col, (uint32_t)take, p.scale, base + used,
+                                    bad && first ? g->bad_dev : nullptr,
+                                    bad && first ? (int32_t*)g->pin : nullptr, g->stream));
+            first = false;
+            return (int)FDTD_OK;
+        });
+        if (e) return e;
+        HIP_OR_FAIL(hipEventRecord(g->pin_ev[half], g->stream));
+        queued[half] = true;
     }
     if (int e = drain(half)) return e;
     if (int e = drain(half ^ 1)) return e;
@@ -2790,22 +2797,23 @@ int fdtd_save_state(fdtd_grid* g, void* host_buf, int64_t bytes)
                                      g->d.max_steps, g->plane_k, (int64_t)g->plane_freqs.size()};
     memcpy(p, hdr, kStateHeader);
     p += kStateHeader;
-    std::vector<Piece> pc;
+    Piece pc[15];
+    int npc = 0;
     for (int c = 0; c < 12; ++c) {
-        pc.push_back(field_piece(g, c, 0, g->d.nz + 1, 1.0, p));
+        pc[npc++] = field_piece(g, c, 0, g->d.nz + 1, 1.0, p);
         p += g->nodes * 4;
     }
     const int64_t np = (int64_t)g->probes.size(), nf = (int64_t)g->freqs.size();
     if (np) {
-        pc.push_back(Piece{g->prb_series, 4, 1, np * g->d.max_steps, np * g->d.max_steps, 1.0, p});
+        pc[npc++] = Piece{g->prb_series, 4, 1, np * g->d.max_steps, np * g->d.max_steps, 1.0, p};
         p += np * g->d.max_steps * 4;
     }
     if (np && nf)
         for (const double* a : {g->dft_re, g->dft_im}) {
-            pc.push_back(Piece{a, 8, 1, np * nf, np * nf, 1.0, p});
+            pc[npc++] = Piece{a, 8, 1, np * nf, np * nf, 1.0, p};
             p += np * nf * 8;
         }
-    if (int e = read_out(g, pc.data(), (int)pc.size())) return e;
+    if (int e = read_out(g, pc, npc)) return e;
     if (g->plane_k >= 0) {
         // the ring is always folded when a call returns: the accumulators are the state
         const int64_t pn = (int64_t)g->plane_freqs.size() * (g->d.nx + 1) * (g->d.ny + 1);
