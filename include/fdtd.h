@@ -95,16 +95,31 @@ typedef struct {
                                     fdtd_set_conductivity, fdtd_set_sheet_resistance) */
     int32_t material_two_step;   /* 1: of which pairs of steps run on the material two-step kernel */
     int32_t material_permille;   /* of its tiles' node planes, the share (per mille) that needs the
-                                    material variant (on small boards whole tiles run it) */
-    int32_t material_split;      /* how: 1 per tile (the variant in the plain kernel's 64 x 14 tiles),
+                                    material variant (what runs, and whether whole tiles do, is told
+                                    by fdtd_get_route) */
+    int32_t material_split;      /* how they are split where whole tiles do not run: 1 per tile (the variant in the plain kernel's 64 x 14 tiles),
                                     2 per plane (planes near material nodes in any tile run the
                                     64 x 10 variant for every tile), 0 no such planes */
     int32_t conduct_permille;    /* the share (per mille) that needs the conduction-only flavour of
-                                    the variant (planes near conducting edges only; boards without
-                                    rebuilt planes run it on every plane) */
+                                    the variant (planes near conducting edges only) */
     int32_t batch_plans;         /* plans of fdtd_step_many calls this handle led, kept for reuse */
     int32_t batch_graphs;        /* of which captured as a graph (one graph launch per call) */
 } fdtd_info;
+
+/* What a handle's pairs of steps run on when it steps alone (fdtd_step_n), once its
+ * set-up is done; all zeros before. */
+typedef struct {
+    int32_t brick_rows, brick_planes;  /* nodes along y and z that a brick owns, where they run in
+                                          bricks (see fdtd_set_tile); 0, 0: they do not */
+    int32_t material_tile_y;     /* material boards on the two-step kernels: tile rows of the material
+                                    variant, 14 or 10; 0 where no tile plane runs it */
+    int32_t whole_tiles;         /* 1: one kernel steps such a board's whole tiles */
+    int64_t plain_planes;        /* tile planes of such a board (each of 64 columns by material_tile_y - 3 */
+    int64_t conduct_planes;      /* rows on the material variant, 11 on the others) that run the plain */
+    int64_t material_planes;     /* kernel, the conduction-only flavour and the material variant */
+    int64_t pinned_bytes;        /* host memory the handle has pinned for results on their way out
+                                    (from its creation on; not part of device_bytes) */
+} fdtd_route;
 
 /* Create a grid (Model section: Yee grid with anisotropic spacing, UPML of
  * Eqs. 1-5 with sigma_max = -(m+1) ln R / (2 eta0 N delta) on each face, outer PEC
@@ -330,6 +345,9 @@ int fdtd_load_state(fdtd_grid* g, const void* host_buf, int64_t bytes);
 
 /* Information about the handle (valid at any time). */
 int fdtd_get_info(fdtd_grid* g, fdtd_info* out);
+
+/* Which kernels the handle's steps run on (valid at any time). */
+int fdtd_get_route(fdtd_grid* g, fdtd_route* out);
 
 /* Tile shape of the field kernel, (tile_x, tile_y, steps) from
  * fdtd_tile_shapes() (Model section: the leapfrog of Eqs. 1-4, fused per pass).

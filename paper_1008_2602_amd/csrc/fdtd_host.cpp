@@ -37,6 +37,7 @@ hipError_t launch_field_step2_material(int tile_y, int mode, const BoardDev* boa
 int field_step2_material_occupancy(int tile_y, int mode, bool wide);
 // fdtd_kernels_brick.hip
 int pick_brick(int nx, int ny, int nz, int cus);
+void brick_owned(int q, int* rows, int* planes);
 hipError_t launch_brick(int q, const BoardDev& b, int par, int rel, bool wide, bool plane, hipStream_t st);
 hipError_t launch_advance(BoardDev* boards, int nb, const int64_t* n, hipStream_t st);
 hipError_t launch_advance_one(int64_t* step, int64_t n, int64_t launches, hipStream_t st);
@@ -2896,6 +2897,28 @@ int fdtd_get_info(fdtd_grid* g, fdtd_info* out)
     out->batch_plans = (int32_t)g->plans.size();
     out->batch_graphs = 0;
     for (const BatchPlan* p : g->plans) out->batch_graphs += p->exec != nullptr;
+    return FDTD_OK;
+}
+
+int fdtd_get_route(fdtd_grid* g, fdtd_route* out)
+{
+    if (int e = check_grid(g)) return e;
+    if (!out) return fail(FDTD_EINVAL, "null output");
+    *out = fdtd_route{};
+    out->pinned_bytes = (int64_t)(kPinHead + 2 * g->pin_room);
+    if (!g->finalized) return FDTD_OK;
+    if (g->brick >= 0) brick_owned(g->brick, &out->brick_rows, &out->brick_planes);
+    if (!g->mat) return FDTD_OK;
+    auto planes = [](const std::vector<TileRef>& pieces) {
+        int64_t n = 0;
+        for (const TileRef& t : pieces) n += t.ke - t.kb;
+        return n;
+    };
+    out->plain_planes = planes(g->pc_plain);
+    out->conduct_planes = planes(g->pc_cd);
+    out->material_planes = planes(g->pc_rb);
+    out->material_tile_y = out->material_planes > 0 ? g->mat_ty : 0;
+    out->whole_tiles = (out->plain_planes > 0) + (out->conduct_planes > 0) + (out->material_planes > 0) == 1;
     return FDTD_OK;
 }
 

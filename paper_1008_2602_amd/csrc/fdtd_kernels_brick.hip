@@ -357,6 +357,13 @@ int pick_brick(int nx, int ny, int nz, int cus)
     return pick;
 }
 
+// Nodes along y and z that a brick of the shape owns.
+void brick_owned(int q, int* rows, int* planes)
+{
+    *rows = kBricks[q].ry - 4;
+    *planes = kBricks[q].rz - 4;
+}
+
 // Two steps of one plain board from field copy `par` to the other; `rel`: steps
 // past the device counter.
 hipError_t launch_brick(int q, const BoardDev& b, int par, int rel, bool wide, bool plane, hipStream_t st)

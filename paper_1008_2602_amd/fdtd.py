@@ -70,6 +70,13 @@ class fdtd_info(C.Structure):
                 ("batch_plans", C.c_int32), ("batch_graphs", C.c_int32)]
 
 
+class fdtd_route(C.Structure):
+    _fields_ = [("brick_rows", C.c_int32), ("brick_planes", C.c_int32),
+                ("material_tile_y", C.c_int32), ("whole_tiles", C.c_int32),
+                ("plain_planes", C.c_int64), ("conduct_planes", C.c_int64),
+                ("material_planes", C.c_int64), ("pinned_bytes", C.c_int64)]
+
+
 class FdtdError(RuntimeError):
     def __init__(self, code: int, msg: str):
         super().__init__(f"libfdtd error {code}: {msg}")
@@ -109,6 +116,7 @@ _sigs = {
     "fdtd_save_state": ([_P, _P, C.c_int64], C.c_int),
     "fdtd_load_state": ([_P, _P, C.c_int64], C.c_int),
     "fdtd_get_info": ([_P, C.POINTER(fdtd_info)], C.c_int),
+    "fdtd_get_route": ([_P, C.POINTER(fdtd_route)], C.c_int),
     "fdtd_set_tile": ([_P, C.c_int, C.c_int, C.c_int], C.c_int),
     "fdtd_tile_shapes": ([_P, C.c_int], C.c_int),
     "fdtd_set_timing": ([_P, C.c_int], C.c_int),
@@ -383,6 +391,12 @@ def board_bytes(board, max_steps: Optional[int] = None) -> int:
 def fdtd_get_info(g) -> fdtd_info:
     out = fdtd_info()
     _check(_lib.fdtd_get_info(g, C.byref(out)))
+    return out
+
+
+def fdtd_get_route(g) -> fdtd_route:
+    out = fdtd_route()
+    _check(_lib.fdtd_get_route(g, C.byref(out)))
     return out
 
 
