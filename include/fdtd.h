@@ -359,10 +359,11 @@ int fdtd_get_route(fdtd_grid* g, fdtd_route* out);
  *     step is recomputed on a two-cell halo and never stored.  An odd step count
  *     ends with one step of the 64x15 one-step shape.
  * Results do not depend on the shape (bitwise).  May be changed between steps;
- * EINVAL for an unsupported shape.  The default is the two-step 64x14; while it
- * has not been set, plain boards of up to a few 10^5 cells take their pairs of
- * steps in bricks of 28 columns by 3 to 12 rows by 3 to 6 planes instead, one
- * compute unit each, where those are faster (the same bits). */
+ * EINVAL for an unsupported shape.  The default is the two-step 64x14; under it
+ * plain boards of up to a few 10^5 cells that step alone take their pairs of steps
+ * in bricks of 28 columns by 4 to 12 rows by 3 to 6 planes instead, one compute
+ * unit each, where those are faster (the same bits; fdtd_get_route tells).  Setting
+ * 64x14x2 returns a handle to that default. */
 int fdtd_set_tile(fdtd_grid* g, int tile_x, int tile_y, int steps);
 
 /* Supported tile shapes: writes up to `cap` triples (tile_x, tile_y, steps) into

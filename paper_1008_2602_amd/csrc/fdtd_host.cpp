@@ -124,6 +124,9 @@ uint32_t fbits(float x)
     return u;
 }
 
+// the field kernels' default shape, which leaves small boards their bricks
+constexpr int kDefaultX = 64, kDefaultY = 14, kDefaultSteps = 2;
+
 }  // namespace
 
 struct fdtd_grid {
@@ -217,8 +220,8 @@ struct fdtd_grid {
     bool wide = false;
     bool finalized = false;
     int64_t step = 0;
-    int tile_x = 64, tile_y = 14, tile_steps = 2;
-    bool tile_set = false;  // by fdtd_set_tile
+    int tile_x = kDefaultX, tile_y = kDefaultY, tile_steps = kDefaultSteps;
+    bool tile_set = false;  // to another shape by fdtd_set_tile
     int brick = -1;         // >= 0: pairs of steps run the small-board kernel in this brick shape
     int par0 = 0;           // field copy at the start of the launches being enqueued (bricks)
     bool recorded = false;  // the caller is recording the call being enqueued into a graph of its own
@@ -1832,7 +1835,7 @@ int fdtd_set_tile(fdtd_grid* g, int tile_x, int tile_y, int steps)
     g->tile_x = tile_x;
     g->tile_y = tile_y;
     g->tile_steps = steps;
-    g->tile_set = true;
+    g->tile_set = !(tile_x == kDefaultX && tile_y == kDefaultY && steps == kDefaultSteps);
     return g->finalized ? upload_tiles(g) : FDTD_OK;
 }
 

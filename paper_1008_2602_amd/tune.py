@@ -1,10 +1,12 @@
 """Tile-shape autotuner for the field kernel.
 
 The field kernel's results do not depend on its tile shape (bitwise), only its
-speed does.  A shape is (tile_x, tile_y, steps per pass); timings are per step.  ``tune_board`` / ``tune_batch`` time every supported shape on
-scratch handles with the same geometry and materials (zero fields, no sources),
-keep the fastest, and cache the choice in a JSON file keyed by the geometry, so
-the live solve never runs a timing step.
+speed does.  A shape is (tile_x, tile_y, steps per pass); timings are per step.
+``tune_board`` / ``tune_batch`` time every supported shape on scratch handles with
+the same geometry and materials (zero fields, no sources), keep the fastest, and
+cache the choice in a JSON file keyed by the geometry, so the live solve never runs
+a timing step.  The default shape 64 x 14 x 2 stands for what an untouched handle
+runs: on small boards bricks, which are timed as such.
 """
 from __future__ import annotations
 
@@ -101,8 +103,15 @@ def _scratch(F, board, steps):
 
 def tune_board(board, steps: int = 6, warm: int = 2, path: Optional[str] = None,
                refresh: bool = False) -> Shape:
+    """The fastest shape for ``board`` stepped alone, over at least ``steps`` steps of
+    each.  Small boards take more (about 4e7 cell-updates), an even number: a step of
+    theirs takes as long as a launch, and what a shape costs is the time its steps
+    take one after another, gaps included, not the time inside its kernels."""
     from . import fdtd as F
     shapes = F.fdtd_tile_shapes()
+    more = int(4e7 / (board.nx * board.ny * board.nz)) // 2 * 2
+    if more > steps:
+        steps = warm = more
     total = len(shapes) * (steps + warm) + 1
 
     def run() -> Shape:
@@ -110,13 +119,12 @@ def tune_board(board, steps: int = 6, warm: int = 2, path: Optional[str] = None,
         try:
             def time_shape(shape):
                 F.fdtd_set_tile(g, *shape)
-                F.fdtd_step_n(g, warm)
-                F.fdtd_set_timing(g, True)
-                F.fdtd_get_timing(g)          # clears
+                F.fdtd_step_n(g, warm)           # builds the shape's graph as well
+                F.fdtd_synchronize(g)
+                t0 = time.perf_counter()
                 F.fdtd_step_n(g, steps)
-                ms, _ = F.fdtd_get_timing(g)
-                F.fdtd_set_timing(g, False)
-                return ms / steps        # per step: a two-step shape makes half the launches
+                F.fdtd_synchronize(g)
+                return (time.perf_counter() - t0) * 1e3 / steps
             best, _ = tune(board_key(board), time_shape, shapes, path, refresh)
             return best
         finally:
