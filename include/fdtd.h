@@ -362,8 +362,11 @@ int fdtd_get_route(fdtd_grid* g, fdtd_route* out);
  * EINVAL for an unsupported shape.  The default is the two-step 64x14; under it
  * plain boards of up to a few 10^5 cells that step alone take their pairs of steps
  * in bricks of 28 columns by 4 to 12 rows by 3 to 6 planes instead, one compute
- * unit each, where those are faster (the same bits; fdtd_get_route tells).  Setting
- * 64x14x2 returns a handle to that default. */
+ * unit each, where those are faster (the same bits; fdtd_get_route tells), unless
+ * several boards step at once whose marching launches share the device better:
+ * while two other handles of the device or more have steps enqueued and not waited
+ * for, or when the call is recorded into a caller's graph.  Setting 64x14x2 returns
+ * a handle to that default. */
 int fdtd_set_tile(fdtd_grid* g, int tile_x, int tile_y, int steps);
 
 /* Supported tile shapes: writes up to `cap` triples (tile_x, tile_y, steps) into

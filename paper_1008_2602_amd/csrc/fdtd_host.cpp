@@ -38,6 +38,7 @@ int field_step2_material_occupancy(int tile_y, int mode, bool wide);
 // fdtd_kernels_brick.hip
 int pick_brick(int nx, int ny, int nz, int cus);
 void brick_owned(int q, int* rows, int* planes);
+double brick_share(int q, int nx, int ny, int nz, int cus);
 hipError_t launch_brick(int q, const BoardDev& b, int par, int rel, bool wide, bool plane, hipStream_t st);
 hipError_t launch_advance(BoardDev* boards, int nb, const int64_t* n, hipStream_t st);
 hipError_t launch_advance_one(int64_t* step, int64_t n, int64_t launches, hipStream_t st);
@@ -224,7 +225,9 @@ struct fdtd_grid {
     bool tile_set = false;  // to another shape by fdtd_set_tile
     int brick = -1;         // >= 0: pairs of steps run the small-board kernel in this brick shape
     int par0 = 0;           // field copy at the start of the launches being enqueued (bricks)
-    bool recorded = false;  // the caller is recording the call being enqueued into a graph of its own
+    bool march = false;     // the call being enqueued runs the marching kernel instead of bricks
+    bool crowd_march = false;  // as every call does while other handles step (upload_tiles)
+    bool stepping = false;  // steps enqueued since the stream was last waited for (g_stepping)
     int cus = 0;            // compute units of the device
     int64_t step_bytes = 0;
 
@@ -235,8 +238,8 @@ struct fdtd_grid {
     int64_t timed_launches = 0;
 
     // graph of kGraphChunk steps (field launches + counter advance), replayed by step_n
-    // (bricks: one per field copy it starts from; else [0])
-    hipGraphExec_t graph_exec[2] = {nullptr, nullptr};
+    // (bricks: [0] and [1], by the field copy it starts from; else [2])
+    hipGraphExec_t graph_exec[3] = {nullptr, nullptr, nullptr};
     bool graph_failed = false;
     hipEvent_t sync_ev = nullptr;
 
@@ -434,6 +437,29 @@ int fill_half(const Piece* pc, int npc, size_t room, Cursor& c, Run run)
     return FDTD_OK;
 }
 
+// Handles with steps enqueued since their stream was last waited for, per device: how
+// many boards step at once (small boards choose their kernel by it, with the same bits).
+constexpr int kDevices = 64;
+constexpr int kCrowd = 2;   // other handles from which on a board marches; beside one other,
+                            // bricks are faster (two boards of 48 x 43 x 30: 6.3 and 8.0 us)
+std::atomic<int> g_stepping[kDevices];
+
+int others_stepping(const fdtd_grid* g)
+{
+    return g_stepping[g->device % kDevices].load(std::memory_order_relaxed) - (g->stepping ? 1 : 0);
+}
+void steps_begin(fdtd_grid* g)
+{
+    if (!g->stepping) g_stepping[g->device % kDevices].fetch_add(1, std::memory_order_relaxed);
+    g->stepping = true;
+}
+// the handle's stream has been waited for
+void steps_end(fdtd_grid* g)
+{
+    if (g->stepping) g_stepping[g->device % kDevices].fetch_sub(1, std::memory_order_relaxed);
+    g->stepping = false;
+}
+
 // Bring results to the host after the work queued on the handle's stream, which
 // has finished when this returns.  The device packs the pieces into one pinned
 // half while the host copies the other one out.  With `bad`, also the watchdog
@@ -480,6 +506,7 @@ int read_out(fdtd_grid* g, const Piece* pc, int npc, int32_t* bad = nullptr)
         HIP_OR_FAIL(hipStreamSynchronize(g->stream));
     }
     if (bad) *bad = *(const int32_t*)g->pin;
+    steps_end(g);
     return FDTD_OK;
 }
 
@@ -1727,9 +1754,10 @@ static int upload_pieces(fdtd_grid* g, int ty, int mode, const std::vector<TileR
     return upload_work(g, tl, dev, n, cap);
 }
 
-static int upload_list(fdtd_grid* g, int tx, int ty, int steps, TileRef** dev, int* n, int* cap)
+static int upload_list(fdtd_grid* g, int tx, int ty, int steps, TileRef** dev, int* n, int* cap,
+                       std::vector<TileRef>& tl)
 {
-    std::vector<TileRef> whole, tl;
+    std::vector<TileRef> whole;
     board_tiles(0, g->d.nx, g->d.ny, g->d.nz, tx, owned_rows(ty, steps), whole);
     build_work(whole, slots_per_xcd(g, tx, ty, steps, g->wide, 0), tl);
     if (tl.empty()) {
@@ -1747,9 +1775,33 @@ static int upload_list(fdtd_grid* g, int tx, int ty, int steps, TileRef** dev, i
     return FDTD_OK;
 }
 
+// Whether a small board marches while several others step, from its marching work list.
+// Beside other launches a brick launch costs its share of the compute units, where up
+// to three marching launches of small boards run side by side (the hardware queues
+// take no more), each as long as its longest piece (2.4 us per pair and plane, with
+// kBlockPlanes more).  Bricks stay where they cost less than 1.5 times that: streams
+// may share a hardware queue, and then marching launches wait for one another (us per
+// step of all, in bricks and marching, own queues: 4 boards of 48 x 43 x 30, 8.1 / 4.8 by
+// this estimate, 12.4 and 9.7; 3 of 64 x 40 x 60, 11.6 / 6.4, 14.1 and 10.5; 5 of 60 x 60 x
+// 30, 9.9 / 5.1, 22.0 and 18.1; kept: 3 of 56 x 24 x 100, 7.7 / 8.8, 10.1 and 13.1; 4 of
+// 112 x 40 x 30, 8.3 / 6.8, 13.4 and 18.0; 8 of 40 x 30 x 20, 4.1 / 4.8, 14.9 and 21.8).
+static bool marches_in_a_crowd(const fdtd_grid* g, const std::vector<TileRef>& list)
+{
+    int blocks = 0, longest = 0;
+    for (const TileRef& t : list)
+        if (t.board >= 0) {
+            ++blocks;
+            longest = std::max(longest, t.ke - t.kb);
+        }
+    const double at_once = std::min(3.0, (double)g->cus / std::max(1, blocks));
+    const double march = 2.4 * (longest + kBlockPlanes) / std::max(1.0, at_once);
+    return brick_share(g->brick, g->d.nx, g->d.ny, g->d.nz, g->cus) > 1.5 * march;
+}
+
 static int upload_tiles(fdtd_grid* g)
 {
     BoardDev& b = g->board_host;
+    std::vector<TileRef> list, odd_list;
     if (g->node_pass) {
         // a material board takes pairs of steps on two-step kernels of one shape,
         // 64 x kHybridTY x 2 (the plain kernel and its material variant), when a
@@ -1796,14 +1848,15 @@ static int upload_tiles(fdtd_grid* g)
             HIP_OR_FAIL(hipEventCreateWithFlags(&g->join_ev, hipEventDisableTiming));
         }
     } else if (int e = upload_list(g, g->tile_x, g->tile_y, g->tile_steps, &g->tiles_dev, &g->ntiles,
-                                   &g->tiles_cap)) {
+                                   &g->tiles_cap, list)) {
         return e;
     }
     if (g->tile_steps == 2 && !g->node_pass)
-        if (int e = upload_list(g, kOddX, kOddY, 1, &g->tiles1_dev, &g->ntiles1, &g->tiles1_cap))
+        if (int e = upload_list(g, kOddX, kOddY, 1, &g->tiles1_dev, &g->ntiles1, &g->tiles1_cap, odd_list))
             return e;
     HIP_OR_FAIL(copy_sync(g, g->board_dev, &b, sizeof(BoardDev), hipMemcpyHostToDevice));
     g->brick = g->tile_set || g->node_pass ? -1 : pick_brick(g->d.nx, g->d.ny, g->d.nz, g->cus);
+    g->crowd_march = g->brick >= 0 && marches_in_a_crowd(g, list);
     for (hipGraphExec_t& e : g->graph_exec) {
         if (e) (void)hipGraphExecDestroy(e);
         e = nullptr;
@@ -1896,7 +1949,7 @@ static int enqueue_launch(fdtd_grid* g, bool single, int rel, int flip)
         if (int e = record_event(g)) return e;
     if (g->mat)
         HIP_OR_FAIL(single ? node_step(g, rel, flip, g->stream) : material_pair(g, rel, flip, g->stream));
-    else if (!single && g->brick >= 0 && !g->recorded)
+    else if (!single && g->brick >= 0 && !g->march)
         HIP_OR_FAIL(launch_brick(g->brick, g->board_host, (g->par0 + flip) & 1, rel, g->wide,
                                  g->plane_k >= 0, g->stream));
     else if (single && g->tile_steps == 2)
@@ -1948,7 +2001,8 @@ static int enqueue_steps(fdtd_grid* g, int64_t n, int64_t* launches)
 static void build_graph(fdtd_grid* g)
 {
     // a brick launch names the field copy it reads
-    hipGraphExec_t& exec = g->graph_exec[g->brick >= 0 ? g->par0 : 0];
+    const bool bricks = g->brick >= 0 && !g->march;
+    hipGraphExec_t& exec = g->graph_exec[bricks ? g->par0 : 2];
     if (exec || g->graph_failed) return;
     g->graph_failed = true;
     if (!g->own_stream && g->stream == nullptr) return;
@@ -1959,7 +2013,7 @@ static void build_graph(fdtd_grid* g)
     for (int l = 0; l < nl && ok; ++l)
         ok = (g->mat         ? material_pair(g, l * per, l & 1, g->stream)
               : g->node_pass ? node_step(g, l, l & 1, g->stream)
-              : g->brick >= 0
+              : bricks
                   ? launch_brick(g->brick, g->board_host, (g->par0 + l) & 1, l * per, g->wide,
                                  g->plane_k >= 0, g->stream)
                              : launch_pass(g->tile_x, g->tile_y, per, g->board_dev, g->tiles_dev,
@@ -2021,16 +2075,19 @@ int fdtd_step_n(fdtd_grid* g, int64_t n)
     // meanwhile are enqueued as plain launches first.  A brick launch (6 us and
     // more on the device, 2.4 us to enqueue) gains nothing from a graph but the
     // host's time, so short calls of such boards go without.
-    const int64_t first = g->brick >= 0 ? 32 * kGraphChunk : kGraphChunk;
-    const bool have = g->graph_exec[g->brick >= 0 ? g->buf : 0] != nullptr;
-    g->recorded = g->brick >= 0 && stream_recorded(g->stream);
-    const bool graph = !g->timing && !g->recorded && n >= kGraphChunk && (have || g->brick < 0 || n >= 2 * first);
+    const bool recorded = g->brick >= 0 && stream_recorded(g->stream);
+    g->march = recorded || (g->crowd_march && others_stepping(g) >= kCrowd);
+    const bool bricks = g->brick >= 0 && !g->march;
+    const int64_t first = bricks ? 32 * kGraphChunk : kGraphChunk;
+    const bool have = g->graph_exec[bricks ? g->buf : 2] != nullptr;
+    const bool graph = !g->timing && !recorded && n >= kGraphChunk && (have || !bricks || n >= 2 * first);
+    if (!recorded) steps_begin(g);
     if (graph && !have && n >= 2 * first)
         if (int e = plain(first)) return e;
     if (graph) {
         g->par0 = (int)((g->buf + launches) & 1);
         build_graph(g);
-        if (hipGraphExec_t exec = g->graph_exec[g->brick >= 0 ? g->par0 : 0]) {
+        if (hipGraphExec_t exec = g->graph_exec[bricks ? g->par0 : 2]) {
             for (; done + kGraphChunk <= n; done += kGraphChunk) {
                 HIP_OR_FAIL(hipGraphLaunch(exec, g->stream));
                 launches += kGraphChunk / (g->node_pass && !g->mat ? 1 : g->tile_steps);
@@ -2630,6 +2687,7 @@ static int probe_spectrum(fdtd_grid* g, int id, int n_fft, double2* a, double* b
     HIP_OR_FAIL(launch_fft(series, g->step, n_fft, a, host, host + nbins, g->bad_dev, (int32_t*)g->pin,
                            g->stream));
     HIP_OR_FAIL(hipStreamSynchronize(g->stream));
+    steps_end(g);
     memcpy(re, host, nbins * 8);
     memcpy(im, host + nbins, nbins * 8);
     if (*(const int32_t*)g->pin)
@@ -2773,6 +2831,7 @@ int fdtd_set_field(fdtd_grid* g, int comp, const float* in)
             }
         }
     HIP_OR_FAIL(hipStreamSynchronize(g->stream));
+    steps_end(g);
     HIP_OR_FAIL(put_field_sync(g, comp_ptr(g, comp), h.data()));
     return FDTD_OK;
 }
@@ -2842,6 +2901,7 @@ int fdtd_load_state(fdtd_grid* g, const void* host_buf, int64_t bytes)
         return fail(FDTD_EINVAL, "state image does not match this grid");
     if (hdr[4] < 0 || hdr[4] > g->d.max_steps) return fail(FDTD_EINVAL, "bad step in state image");
     HIP_OR_FAIL(hipStreamSynchronize(g->stream));
+    steps_end(g);
     g->step = hdr[4];
     for (int c = 0; c < 12; ++c) {
         HIP_OR_FAIL(put_field_sync(g, comp_ptr(g, c), p));
@@ -2937,6 +2997,7 @@ int fdtd_get_timing(fdtd_grid* g, double* ms, int64_t* launches)
     if (int e = check_grid(g)) return e;
     if (!ms || !launches) return fail(FDTD_EINVAL, "null output");
     HIP_OR_FAIL(hipStreamSynchronize(g->stream));
+    steps_end(g);
     double total = 0.0;
     for (size_t t = 0; t + 1 < g->ev_used; t += 2) {
         float v = 0.f;
@@ -2954,6 +3015,7 @@ int fdtd_destroy_grid(fdtd_grid* g)
 {
     if (!g) return FDTD_OK;
     if (g->stream) (void)hipStreamSynchronize(g->stream);
+    steps_end(g);
     for (hipEvent_t e : g->ev_pool) (void)hipEventDestroy(e);
     if (g->pin) give_pin(g->device, g->pin_room, g->pin, !g->d.dev_free);
     for (hipEvent_t e : g->pin_ev)

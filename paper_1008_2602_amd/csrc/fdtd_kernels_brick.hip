@@ -333,6 +333,18 @@ static const struct {
     double us;
 } kBricks[] = {{8, 7, 9.4}, {8, 8, 10.0}, {12, 8, 13.2}, {10, 10, 15.4}, {16, 8, 16.8}};
 
+static double brick_count(int q, int nx, int ny, int nz)
+{
+    return std::ceil(nx / 28.0) * std::ceil(ny / (kBricks[q].ry - 4.0)) * std::ceil(nz / (kBricks[q].rz - 4.0));
+}
+
+// What a pair of steps in bricks of shape q costs a device that other launches keep
+// busy (microseconds): its share of the compute units for a brick's time.
+double brick_share(int q, int nx, int ny, int nz, int cus)
+{
+    return kBricks[q].us * brick_count(q, nx, ny, nz) / std::max(1, cus);
+}
+
 // The brick shape for a plain board, -1 where the marching kernel is faster.  A
 // second round of bricks costs as much as the first (80 x 72 x 37 cells in 540
 // 8 x 8 bricks: 20.8 us; in 252 of 10 x 10: 15.9).  The marching kernel's pair
@@ -346,9 +358,7 @@ int pick_brick(int nx, int ny, int nz, int cus)
     double best = 0.95 * (16.0 + 3.2e-5 * std::max(0.0, cells - 1e5));
     int pick = -1;
     for (int q = 0; q < (int)(sizeof(kBricks) / sizeof(kBricks[0])); ++q) {
-        const double bricks = std::ceil(nx / 28.0) * std::ceil(ny / (kBricks[q].ry - 4.0)) *
-                              std::ceil(nz / (kBricks[q].rz - 4.0));
-        const double us = kBricks[q].us * std::ceil(bricks / std::max(1, cus));
+        const double us = kBricks[q].us * std::ceil(brick_count(q, nx, ny, nz) / std::max(1, cus));
         if (us < best) {
             best = us;
             pick = q;
