@@ -522,6 +522,8 @@ int owned_rows(int ty, int steps) { return steps == 2 ? ty - 3 : ty - 1; }
 
 // The one-step shape that takes the odd step of a two-step shape.
 constexpr int kOddX = 64, kOddY = 15;
+// whether a launch of the shape takes build_work's rule for one-step shapes
+bool one_step_list(int tx, int ty, int steps) { return steps == 1 && !(tx == kOddX && ty == kOddY); }
 
 // Tiles of a shape: tx aligned columns and `rows` owned rows each.  The tiles
 // cover node columns 0..nx-1 and rows 0..ny-1 (and the kernels step planes
@@ -634,10 +636,20 @@ TileRef piece_of(TileRef t, int q, int n)
 // last full round of concurrent blocks would leave most of the XCD idle in that
 // round, and are split into S pieces (S chosen to shorten the estimated tail).
 //
+// `one_step`: the list of a one-step shape but 64 x 15.  Its blocks are two or more to a
+// compute unit and start sooner (one recomputed plane, no loads two planes ahead), so
+// shorter pieces in more rounds suit them: all its launches take the second rule, with
+// a start counted as one plane (444 x 364 x 60 in 64 x 14: 157 us per step, 168 by the
+// first rule; in 64 x 4 180 and 195; 301 x 283 x 44 in 64 x 12 68 and 72; 400 x 100 x 100
+// in 128 x 5 80 and 83).  64 x 15, which also takes the odd last step of the two-step
+// shapes, is faster by the first (200 x 200 x 60 39 and 36, 120 x 110 x 50 16.7 and 15.9,
+// 260 x 250 x 30 36.0 and 34.6; 301 x 283 x 44 70.3 and 71.2).
+//
 // Pieces go piece-major so that concurrent pieces are spatial neighbours at the
 // same depth.  Every run is padded with idle entries to the common length, so the
 // launch has kXcds * length blocks.
-void build_work(const std::vector<TileRef>& tiles, int slots_per_xcd, std::vector<TileRef>& out)
+void build_work(const std::vector<TileRef>& tiles, int slots_per_xcd, std::vector<TileRef>& out,
+                bool one_step = false)
 {
     out.clear();
     const size_t T = tiles.size();
@@ -648,7 +660,7 @@ void build_work(const std::vector<TileRef>& tiles, int slots_per_xcd, std::vecto
     int deepest = 1;
     for (size_t q = 0; q < T; ++q) deepest = std::max(deepest, w[q] = tiles[q].ke - tiles[q].kb);
     size_t end[kXcds];
-    if (T <= (size_t)C * kXcds) {
+    if (T <= (size_t)C * kXcds && !one_step) {
         double best = HUGE_VAL;
         std::fill(w.begin(), w.end(), 0);
         for (int p = deepest; p >= 1; --p) {
@@ -693,11 +705,12 @@ void build_work(const std::vector<TileRef>& tiles, int slots_per_xcd, std::vecto
             int S = 1;
             if (m > 0) {
                 const double pbar = std::accumulate(w.begin() + (idx - m), w.begin() + idx, 0.0) / (double)m;
-                double best = pbar + kBlockPlanes;
+                double best = one_step ? pbar : pbar + kBlockPlanes;
                 for (int cand = 2; cand <= kMaxPieces && pbar / cand >= 2.0; ++cand) {
                     const double rounds = std::ceil((double)(m * cand) / (double)C);
-                    const double cost = rounds * (std::ceil(pbar / cand) + kBlockPlanes);
-                    if (cost < best) {
+                    const double cost = rounds * (one_step ? pbar / cand + 1.0
+                                                           : std::ceil(pbar / cand) + kBlockPlanes);
+                    if (cost < (one_step ? 0.97 : 1.0) * best) {
                         best = cost;
                         S = cand;
                     }
@@ -1759,7 +1772,7 @@ static int upload_list(fdtd_grid* g, int tx, int ty, int steps, TileRef** dev, i
 {
     std::vector<TileRef> whole;
     board_tiles(0, g->d.nx, g->d.ny, g->d.nz, tx, owned_rows(ty, steps), whole);
-    build_work(whole, slots_per_xcd(g, tx, ty, steps, g->wide, 0), tl);
+    build_work(whole, slots_per_xcd(g, tx, ty, steps, g->wide, 0), tl, one_step_list(tx, ty, steps));
     if (tl.empty()) {
         *n = 0;
         return FDTD_OK;
@@ -2256,7 +2269,8 @@ void plan_round(fdtd_grid* const* gs, int ng, const int64_t* n, RoundHost& r)
                             }
                     }
                     if (whole.empty()) continue;
-                    build_work(whole, slots_per_xcd(lead, ktx, kty, kper, w == 1, mode), list);
+                    build_work(whole, slots_per_xcd(lead, ktx, kty, kper, w == 1, mode), list,
+                               one_step_list(ktx, kty, kper));
                     sp.kind[sp.nl] = kind;
                     sp.off[sp.nl] = (int)r.items.size();
                     sp.count[sp.nl] = (int)list.size();
