@@ -128,7 +128,12 @@ typedef struct {
  * of a field share one 4 GiB window), non-positive spacing, dt at or above the
  * Eq. 7 limit (c0),
  * courant outside (0, 1), npml < 0 or two opposite layers overlapping,
- * max_steps < 1.  ENOMEM: device allocation failed (no handle is returned). */
+ * max_steps < 1.  ENOMEM: an allocation failed (no handle is returned).  A handle also
+ * pins 1 to 4 MiB of host memory that results pass through (fdtd_route.pinned_bytes;
+ * not in device_bytes or fdtd_estimate_bytes).  The library keeps up to 256 MiB of
+ * released such buffers for its next handles; they are freed with the last handle,
+ * unless that one's device memory comes from dev_alloc, whose release then waits for
+ * no other work on the device. */
 int fdtd_create_grid(const fdtd_grid_desc* desc, fdtd_grid** out);
 
 /* Materials (Model section, Fig. 1): eps_r_cell (host, nx*ny*nz floats, x fastest,

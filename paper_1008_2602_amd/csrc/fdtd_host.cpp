@@ -986,16 +986,22 @@ void split_material(int nx, int ny, int nz, const std::vector<uint8_t>& tile_nee
 // no more; the shares stay those of the planes that do).
 //  * Boards with conducting edges only: always.  Beside the field arithmetic the
 //    conduction-only flavour costs nothing (114 VGPRs, nothing spilled; 444 x 364 x 60
-//    with a lossy layer between sheets 82 us per step as the lossless board, 1048 x
-//    792 x 88 552; split 115-122 and 659 before either kernel was sped up), while
+//    with a lossy layer between sheets 82 us per step as the lossless board, 8 of
+//    them in a batch 610, 1048 x 792 x 88 552; split 115-122, 783 and 659 before either
+//    kernel was sped up), while
 //    pieces re-read their halo planes, run in two launches that crowd each other's
 //    compute units out, and join two streams every pair.
 //  * Boards with rebuilt PML coefficients: up to about 200 tile planes per compute
-//    unit.  The material variant runs whole tiles at 1.06-1.15 times the plain
-//    kernel's time (us per step, whole and split: 444 x 364 x 60 95 and 104; 600 x
-//    412 x 60 139 and 163; 800 x 500 x 60 208 and 220; 900 x 600 x 60, 193 planes,
-//    277 and 297), which is more than the split loses on larger boards (1000 x 700 x
-//    60, 240 planes, 372 and 335; 1048 x 792 x 88 591 and 577).
+//    unit.  With a slab through the x/y PML the material variant runs whole tiles at
+//    1.06-1.15 times the plain kernel's time (us per step, whole and split: 444 x 364 x
+//    60 95 and 104; 600 x 412 x 60 136 and 159; 800 x 500 x 60 208 and 220; 900 x 600 x
+//    60, 193 planes, 274 and 292); on larger boards the split loses about as much and
+//    sometimes less (1000 x 700 x 60, 240 planes, 367 and 334; 1200 x 900 x 60 513 and
+//    507; 1048 x 792 x 88 562 and 575).  Where every PML node is rebuilt whole tiles gain
+//    more (300 x 250 x 60 72 and 94, 444 x 364 x 60 135 and 163, 1048 x 792 x 88, past the
+//    line, 653 and 823).  In a batched call the boards keep the pieces they have alone,
+//    which costs 0.6 % at most: 2, 4 and 8 boards of 600 x 412 x 60 257, 504 and 977,
+//    split 282, 507 and 971; 8 filled ones of 444 x 364 x 60 763 and 971.
 constexpr int kMaterialWholePlanes = 200;
 void one_kernel_board(int nx, int ny, int nz, int cus, MaterialSplit& ms)
 {

@@ -720,7 +720,7 @@ struct Shape2 {
     int tx, ty;
 };
 // 64*TY + 128 threads.  All shapes fit 120 VGPRs, four waves per SIMD, without
-// spilling (116-117, 119 in the plane-DFT variant): TY = 14 fills a compute unit
+// spilling (116-118, 119-120 in the plane-DFT variant): TY = 14 fills a compute unit
 // with one block, two 512-thread blocks of TY = 6 share one, and between them one
 // block leaves wave slots idle.  Taller tiles recompute fewer halo rows per owned
 // row.

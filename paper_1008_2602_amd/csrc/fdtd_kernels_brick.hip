@@ -17,11 +17,12 @@
 // marching kernel (field_step2) walks such a board's few tiles in short z pieces,
 // three barriers and a round of prefetched loads per plane behind a chain of five
 // dependent loads (work item, descriptor, step counters, tables, fields):
-// 15.0 us per pair of steps for 48 x 43 x 30 cells (9.6 in bricks) where an empty
-// launch takes 1.7.  Here a brick's loads are all in flight at once, addressed from kernel
-// arguments alone, and a pair of steps is five barriers.  The price is the
-// halo: 22 % (RY = RZ = 8) to 33 % of the nodes computed are owned, which is why
-// larger boards, whose compute units are busy anyway, keep the marching kernel.
+// 14.7 us per pair of steps for 48 x 43 x 30 cells (9.5 in bricks) where a chain of empty
+// launches takes 1.7 each.  Here a brick's loads are all in flight at once, addressed from
+// kernel arguments alone, and a pair of steps is four barriers.  The price is the
+// halo: 19 % (8 x 7) to 33 % (16 x 8) of the nodes computed are owned, which is why
+// larger boards, whose compute units are busy anyway, keep the marching kernel, and
+// so do boards that step beside others whose launches could share the device.
 //
 // Every per-node update is written with exactly the expressions of the other
 // field kernels, so all give the same bits.
@@ -349,9 +350,9 @@ double brick_share(int q, int nx, int ny, int nz, int cus)
 // second round of bricks costs as much as the first (80 x 72 x 37 cells in 540
 // 8 x 8 bricks: 20.8 us; in 252 of 10 x 10: 15.9).  The marching kernel's pair
 // takes 15 to 16 us up to about 100 k cells and up to 3.2 us more per further 100 k
-// (48 x 43 x 30: 15.0, bricks 9.6; 80 x 72 x 37: 18.3 and 15.9; 130 x 60 x 40: 21.2
-// and 18.0); it is left where it is within 5 % of the estimate.  Over 21 boards of
-// 6 k to 360 k cells the choice was never the slower one.
+// (48 x 43 x 30: 14.7, bricks 9.5; 80 x 72 x 37: 18.2 and 15.9; 130 x 60 x 40: 21.0
+// and 17.9); it is left where it is within 5 % of the estimate.  Over 21 boards of
+// 6 k to 360 k cells that stepped alone the choice was never the slower one.
 int pick_brick(int nx, int ny, int nz, int cus)
 {
     const double cells = (double)nx * ny * nz;
