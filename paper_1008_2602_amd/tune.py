@@ -138,18 +138,25 @@ def tune_board(board, steps: int = 6, warm: int = 2, path: Optional[str] = None,
 
 def tune_batch(boards: Sequence, steps: int = 4, warm: int = 1, path: Optional[str] = None,
                refresh: bool = False) -> Shape:
+    """The fastest lead shape for ``boards`` stepped in one call, over at least ``steps``
+    steps of each (small batches more: about 4e8 cell-updates).  A call's plan is built
+    by its first use, so every shape is warmed up by the very call that is timed."""
     from . import fdtd as F
     key = batch_key(boards)
     shapes = F.fdtd_tile_shapes()
     hit = cached(key, shapes, path)
     if hit is not None and not refresh:
         return hit
-    total = len(shapes) * (steps + warm) + 1
+    cells = sum(b.nx * b.ny * b.nz for b in boards)
+    steps = max(steps, int(4e8 / cells) // 2 * 2)
+    total = len(shapes) * (2 * steps + warm) + 1
     gs = [_scratch(F, b, total) for b in boards]
     try:
         def time_shape(shape):
             F.fdtd_set_tile(gs[0], *shape)
-            F.fdtd_step_many(gs, [warm] * len(gs))
+            if warm:
+                F.fdtd_step_many(gs, [warm] * len(gs))
+            F.fdtd_step_many(gs, [steps] * len(gs))
             F.fdtd_synchronize(gs[0])
             t0 = time.perf_counter()
             F.fdtd_step_many(gs, [steps] * len(gs))
