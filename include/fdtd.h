@@ -113,7 +113,8 @@ typedef struct {
                                           bricks (see fdtd_set_tile); 0, 0: they do not */
     int32_t material_tile_y;     /* material boards on the two-step kernels: tile rows of the material
                                     variant, 14 or 10; 0 where no tile plane runs it */
-    int32_t whole_tiles;         /* 1: one kernel steps such a board's whole tiles */
+    int32_t whole_tiles;         /* 1: one kernel steps such a board's whole tiles (this and the following:
+                                    in fdtd_step_n; a batched call chooses for its boards together) */
     int64_t plain_planes;        /* tile planes of such a board (each of 64 columns by material_tile_y - 3 */
     int64_t conduct_planes;      /* rows on the material variant, 11 on the others) that run the plain */
     int64_t material_planes;     /* kernel, the conduction-only flavour and the material variant */

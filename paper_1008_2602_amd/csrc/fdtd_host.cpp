@@ -10,6 +10,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <numeric>
 #include <string>
@@ -130,6 +131,15 @@ constexpr int kDefaultX = 64, kDefaultY = 14, kDefaultSteps = 2;
 
 }  // namespace
 
+// How a material board's pairs of steps are split between the plain two-step
+// kernel and the material variants.
+struct MaterialSplit {
+    std::vector<TileRef> rb, cd, plain;   // material variant, conduction-only flavour, plain kernel
+    int mat_ty = kHybridTY;               // the material variant's tile rows
+    int split = 0;                        // 0 none, 1 per tile, 2 per plane
+    int mat_permille = 0, cond_permille = 0;
+};
+
 struct fdtd_grid {
     fdtd_grid_desc d{};
     double dt = 0.0;
@@ -186,6 +196,7 @@ struct fdtd_grid {
     int tilesP_cap = 0;
     // the same pieces on the host (board index 0), for batched calls
     std::vector<TileRef> pc_plain, pc_cd, pc_rb;
+    std::unique_ptr<MaterialSplit> either;   // the split, where whole_tiles_win chooses
     TileRef* tilesC_dev = nullptr;  // pieces of the conduction-only flavour (64 x kHybridTY x 2)
     int ntilesC = 0;
     int tilesC_cap = 0;
@@ -884,15 +895,6 @@ void mark_tile_need(const uint8_t* need, int nx, int ny, uint8_t bit, std::vecto
         }
 }
 
-// How a material board's pairs of steps are split between the plain two-step
-// kernel and the material variants.
-struct MaterialSplit {
-    std::vector<TileRef> rb, cd, plain;   // material variant, conduction-only flavour, plain kernel
-    int mat_ty = kHybridTY;               // the material variant's tile rows
-    int split = 0;                        // 0 none, 1 per tile, 2 per plane
-    int mat_permille = 0, cond_permille = 0;
-};
-
 // The split of a board of nx x ny x nz cells from tile_need (per tile of the
 // 64 x kHybridTY x 2 grid and node plane, bits 1 rebuilt coefficients, 2
 // conduction; empty: none).  A piece [kb, ke) of a tile computes first-step H
@@ -981,9 +983,9 @@ void split_material(int nx, int ny, int nz, const std::vector<uint8_t>& tile_nee
     out.cond_permille = (int)(1000.0 * cd_tp / all);
 }
 
-// Where one kernel over whole tiles beats the split above, make its pieces the
-// whole board's tiles (every kernel gives the plain one's bits on planes that need
-// no more; the shares stay those of the planes that do).
+// Where one kernel over whole tiles beats the split above, the pieces are the whole
+// board's tiles (every kernel gives the plain one's bits on planes that need no more;
+// the shares stay those of the planes that do).
 //  * Boards with conducting edges only: always.  Beside the field arithmetic the
 //    conduction-only flavour costs nothing (114 VGPRs, nothing spilled; 444 x 364 x 60
 //    with a lossy layer between sheets 82 us per step as the lossless board, 8 of
@@ -992,28 +994,95 @@ void split_material(int nx, int ny, int nz, const std::vector<uint8_t>& tile_nee
 //    pieces re-read their halo planes, run in two launches that crowd each other's
 //    compute units out, and join two streams every pair.
 //  * Boards with rebuilt PML coefficients: up to about 200 tile planes per compute
-//    unit.  With a slab through the x/y PML the material variant runs whole tiles at
-//    1.06-1.15 times the plain kernel's time (us per step, whole and split: 444 x 364 x
-//    60 95 and 104; 600 x 412 x 60 136 and 159; 800 x 500 x 60 208 and 220; 900 x 600 x
-//    60, 193 planes, 274 and 292); on larger boards the split loses about as much and
-//    sometimes less (1000 x 700 x 60, 240 planes, 367 and 334; 1200 x 900 x 60 513 and
-//    507; 1048 x 792 x 88 562 and 575).  Where every PML node is rebuilt whole tiles gain
-//    more (300 x 250 x 60 72 and 94, 444 x 364 x 60 135 and 163, 1048 x 792 x 88, past the
-//    line, 653 and 823).  In a batched call the boards keep the pieces they have alone,
-//    which costs 0.6 % at most: 2, 4 and 8 boards of 600 x 412 x 60 257, 504 and 977,
-//    split 282, 507 and 971; 8 filled ones of 444 x 364 x 60 763 and 971.
+//    unit, where whole_tiles_win.  With a slab through the x/y PML the material variant
+//    runs whole tiles at 1.06-1.15 times the plain kernel's time (us per step, whole and
+//    split: 444 x 364 x 60 95 and 104; 600 x 412 x 60 136 and 159; 800 x 500 x 60 208 and
+//    220; 900 x 600 x 60, 193 planes, 274 and 292); on larger boards the split loses about
+//    as much and sometimes less (1000 x 700 x 60, 240 planes, 367 and 334; 1200 x 900 x 60
+//    513 and 507; 1048 x 792 x 88 562 and 575).  Where every PML node is rebuilt whole
+//    tiles gain more (300 x 250 x 60 72 and 94, 444 x 364 x 60 135 and 163, 1048 x 792 x
+//    88, past the line, 653 and 823).
 constexpr int kMaterialWholePlanes = 200;
-void one_kernel_board(int nx, int ny, int nz, int cus, MaterialSplit& ms)
+bool may_run_whole(int nx, int ny, int nz, int cus, const MaterialSplit& ms)
 {
     int cx, cy;
     tile_counts(nx, ny, 64, owned_rows(kHybridTY, 2), &cx, &cy);
+    return ms.rb.empty() ? !ms.cd.empty() : (int64_t)cx * cy * nz <= (int64_t)kMaterialWholePlanes * cus;
+}
+
+// Make the pieces the board's whole tiles.
+void run_whole(int nx, int ny, int nz, MaterialSplit& ms)
+{
     const bool rebuilt = !ms.rb.empty();
-    if (rebuilt ? (int64_t)cx * cy * nz > (int64_t)kMaterialWholePlanes * cus : ms.cd.empty()) return;
     ms.rb.clear();
     ms.cd.clear();
     ms.plain.clear();
     board_tiles(0, nx, ny, nz, 64, owned_rows(kHybridTY, 2), rebuilt ? ms.rb : ms.cd);
     if (rebuilt) ms.mat_ty = kHybridTY;
+}
+
+// A board with rebuilt coefficients that may run whole, with its split.
+struct EitherWay {
+    int nx, ny, nz;
+    const MaterialSplit* split;
+};
+
+// Whether such boards, stepped in one launch per kind, run whole 64 x kHybridTY material
+// tiles.  With more than 16 (on 256 compute units) they do.  Fewer, each cut into
+// kMaxPieces at most, last as long as the longest piece (us per step, whole and split):
+//  * Boards rebuilt everywhere, whose split is whole 64 x kMatTY tiles: a plane of these
+//    takes 0.86 of the time (they spill nothing), so they win unless their larger number
+//    costs more rounds or longer pieces (56 x 39 x 48 15.8 and 13.6; 27 x 45 x 65 20.0 and
+//    17.0; 26 x 101 x 36 15.4 and 13.1; 80 x 72 x 37 15.6 and 15.8; 128 x 77 x 60 17.9 and
+//    18.9; 4 boards of 56 x 39 x 48 17.7 and 19.2, of 20 x 35 x 50 18.6 and 17.5; past
+//    the line 9 of them 30.6 and 28.5, 200 x 200 x 60 50 and 62).
+//  * Others, up to 8 tiles: pieces of a kind are cut once more, so that a few deep tiles
+//    gain by the split (64 x 32 x 86, 3 tiles, a slab 16.4 and 12.5, half the planes 19.8
+//    and 14.6; 60 x 60 x 100 17.9 and 13.5) and shallow ones (two planes a piece: 48 x 43
+//    x 30 11.7 and 12.9) or more of them mostly do not (80 x 72 x 37, 14 tiles, 13.4 and
+//    14.9; 26 x 101 x 36, 10 tiles, 13.1 and 12.7, half the planes 14.3 and 16.2; 2, 4
+//    and 8 boards of 600 x 412 x 60 257, 504 and 977, split 282, 507 and 971).
+bool whole_tiles_win(const std::vector<EitherWay>& boards, int cus)
+{
+    std::vector<TileRef> whole, split, list;
+    bool filled = true;
+    for (const EitherWay& b : boards) {
+        board_tiles(0, b.nx, b.ny, b.nz, 64, owned_rows(kHybridTY, 2), whole);
+        split.insert(split.end(), b.split->rb.begin(), b.split->rb.end());
+        filled &= b.split->plain.empty() && b.split->cd.empty() && b.split->mat_ty == kMatTY;
+    }
+    const int C = std::max(1, cus / kXcds);
+    int longest = 0;
+    auto cost = [&](const std::vector<TileRef>& tiles) {
+        build_work(tiles, C, list);
+        longest = 0;
+        for (const TileRef& t : list)
+            if (t.board >= 0) longest = std::max(longest, t.ke - t.kb);
+        return std::ceil((double)list.size() / (kXcds * C)) * (longest + kBlockPlanes);
+    };
+    if (whole.size() * 16 > (size_t)cus) return true;
+    if (filled) return cost(whole) <= 0.86 * cost(split);
+    cost(whole);
+    return whole.size() * 32 > (size_t)cus || longest < 3;
+}
+
+// The pieces of a material board's pairs of steps: alone (pc_*, and the shares reported),
+// and the split it may still take in a batched call (either).
+void material_pieces(fdtd_grid* g)
+{
+    MaterialSplit ms;
+    split_material(g->d.nx, g->d.ny, g->d.nz, g->tile_need, ms);
+    const bool may = may_run_whole(g->d.nx, g->d.ny, g->d.nz, g->cus, ms);
+    g->either.reset(may && !ms.rb.empty() ? new MaterialSplit(ms) : nullptr);
+    if (may && (!g->either || whole_tiles_win({EitherWay{g->d.nx, g->d.ny, g->d.nz, &ms}}, g->cus)))
+        run_whole(g->d.nx, g->d.ny, g->d.nz, ms);
+    g->mat_ty = ms.mat_ty;
+    g->mat_split = ms.split;
+    g->mat_permille = ms.mat_permille;
+    g->cond_permille = ms.cond_permille;
+    g->pc_plain.swap(ms.plain);
+    g->pc_cd.swap(ms.cd);
+    g->pc_rb.swap(ms.rb);
 }
 
 int64_t count_step_bytes(const fdtd_grid* g)
@@ -1845,21 +1914,12 @@ static int upload_tiles(fdtd_grid* g)
         // of the plain kernel, the rest the plain kernel (split_material).  The
         // kernels read one field copy and write the other, each its own pieces'
         // nodes, and give the node passes' bits.
-        MaterialSplit ms;
-        split_material(g->d.nx, g->d.ny, g->d.nz, g->tile_need, ms);
-        one_kernel_board(g->d.nx, g->d.ny, g->d.nz, g->cus, ms);
-        g->mat_ty = ms.mat_ty;
-        g->mat_split = ms.split;
-        g->mat_permille = ms.mat_permille;
-        g->cond_permille = ms.cond_permille;
-        g->pc_plain = ms.plain;
-        g->pc_cd = ms.cd;
-        g->pc_rb = ms.rb;
-        if (int e = upload_pieces(g, g->mat_ty, 1, ms.rb, &g->tiles_dev, &g->ntiles, &g->tiles_cap))
+        material_pieces(g);
+        if (int e = upload_pieces(g, g->mat_ty, 1, g->pc_rb, &g->tiles_dev, &g->ntiles, &g->tiles_cap))
             return e;
-        if (int e = upload_pieces(g, kHybridTY, 2, ms.cd, &g->tilesC_dev, &g->ntilesC, &g->tilesC_cap))
+        if (int e = upload_pieces(g, kHybridTY, 2, g->pc_cd, &g->tilesC_dev, &g->ntilesC, &g->tilesC_cap))
             return e;
-        if (int e = upload_pieces(g, kHybridTY, 0, ms.plain, &g->tilesP_dev, &g->ntilesP, &g->tilesP_cap))
+        if (int e = upload_pieces(g, kHybridTY, 0, g->pc_plain, &g->tilesP_dev, &g->ntilesP, &g->tilesP_cap))
             return e;
         if (g->ntilesP > 0 && g->ntiles + g->ntilesC > 0 && !g->aux_stream) {
             HIP_OR_FAIL(hipStreamCreateWithFlags(&g->aux_stream, hipStreamNonBlocking));
@@ -2251,6 +2311,12 @@ void plan_round(fdtd_grid* const* gs, int ng, const int64_t* n, RoundHost& r)
                 // list (and a launch per pass) of its own
                 Span sp{w, mat ? 2 : per, s, s_end};
                 sp.tail = false;
+                std::vector<EitherWay> either;
+                for (int b = b0; mat && b < active; ++b) {
+                    const fdtd_grid* g = gs[r.order[b]];
+                    if (g->either) either.push_back(EitherWay{g->d.nx, g->d.ny, g->d.nz, g->either.get()});
+                }
+                const bool run_them_whole = !either.empty() && whole_tiles_win(either, lead->cus);
                 for (int kind = mat ? 1 : 0; kind <= (mat ? 4 : 0); ++kind) {
                     const int kty = kind == 0 ? ty : kind == 4 ? kMatTY : kHybridTY;
                     const int ktx = kind == 0 ? tx : 64, kper = kind == 0 ? per : 2;
@@ -2262,12 +2328,18 @@ void plan_round(fdtd_grid* const* gs, int ng, const int64_t* n, RoundHost& r)
                             board_tiles(b, g->d.nx, g->d.ny, g->d.nz, tx, owned_rows(ty, per), whole);
                             continue;
                         }
+                        if (g->either && run_them_whole) {
+                            if (kind == 3)
+                                board_tiles(b, g->d.nx, g->d.ny, g->d.nz, 64, owned_rows(kHybridTY, 2), whole);
+                            continue;
+                        }
+                        const MaterialSplit* ei = g->either.get();
                         const std::vector<TileRef>* pc =
-                            kind == 1 ? &g->pc_plain
-                                      : kind == 2 ? &g->pc_cd
-                                                  : (g->mat_ty == (kind == 3 ? kHybridTY : kMatTY)
-                                                         ? &g->pc_rb
-                                                         : nullptr);
+                            kind == 1   ? (ei ? &ei->plain : &g->pc_plain)
+                            : kind == 2 ? (ei ? &ei->cd : &g->pc_cd)
+                            : (ei ? ei->mat_ty : g->mat_ty) == (kind == 3 ? kHybridTY : kMatTY)
+                                ? (ei ? &ei->rb : &g->pc_rb)
+                                : nullptr;
                         if (pc)
                             for (TileRef t : *pc) {
                                 t.board = b;
