@@ -1028,20 +1028,22 @@ struct EitherWay {
 };
 
 // Whether such boards, stepped in one launch per kind, run whole 64 x kHybridTY material
-// tiles.  With more than 16 (on 256 compute units) they do.  Fewer, each cut into
-// kMaxPieces at most, last as long as the longest piece (us per step, whole and split):
+// tiles.  While few blocks are in flight, tiles cut into kMaxPieces or pieces of two
+// planes at most, a launch lasts as long as its longest piece (us per step, whole and
+// split):
 //  * Boards rebuilt everywhere, whose split is whole 64 x kMatTY tiles: a plane of these
-//    takes 0.86 of the time (they spill nothing), so they win unless their larger number
-//    costs more rounds or longer pieces (56 x 39 x 48 15.8 and 13.6; 27 x 45 x 65 20.0 and
-//    17.0; 26 x 101 x 36 15.4 and 13.1; 80 x 72 x 37 15.6 and 15.8; 128 x 77 x 60 17.9 and
-//    18.9; 4 boards of 56 x 39 x 48 17.7 and 19.2, of 20 x 35 x 50 18.6 and 17.5; past
-//    the line 9 of them 30.6 and 28.5, 200 x 200 x 60 50 and 62).
-//  * Others, up to 8 tiles: pieces of a kind are cut once more, so that a few deep tiles
-//    gain by the split (64 x 32 x 86, 3 tiles, a slab 16.4 and 12.5, half the planes 19.8
-//    and 14.6; 60 x 60 x 100 17.9 and 13.5) and shallow ones (two planes a piece: 48 x 43
-//    x 30 11.7 and 12.9) or more of them mostly do not (80 x 72 x 37, 14 tiles, 13.4 and
-//    14.9; 26 x 101 x 36, 10 tiles, 13.1 and 12.7, half the planes 14.3 and 16.2; 2, 4
-//    and 8 boards of 600 x 412 x 60 257, 504 and 977, split 282, 507 and 971).
+//    takes 0.86 of the time (they spill nothing), so they win where their pieces run in
+//    one round and are not longer for it (56 x 39 x 48 15.8 and 13.6; 27 x 45 x 65 20.0
+//    and 17.0; 15 x 228 x 11 14.2 and 12.2; 128 x 77 x 60 17.9 and 18.9; 200 x 200 x 60 50
+//    and 62; 4 boards of 128 x 386 x 20, where both take rounds, 60 and 78).  Over 197
+//    boards and batches the choice is 0.1 % behind the better of both on average.
+//  * Others, up to 8 tiles on 256 compute units: pieces of a kind are cut once more, so
+//    that a few deep tiles gain by the split (64 x 32 x 86, 3 tiles, a slab 16.4 and 12.5,
+//    half the planes 19.8 and 14.6; 60 x 60 x 100 17.9 and 13.5) and shallow ones (two
+//    planes a piece: 48 x 43 x 30 11.7 and 12.9) or more of them mostly do not (80 x 72 x
+//    37, 14 tiles, 13.4 and 14.9; 26 x 101 x 36, 10 tiles, 13.1 and 12.7, half the planes
+//    14.3 and 16.2; 2, 4 and 8 boards of 600 x 412 x 60 257, 504 and 977, split 282, 507
+//    and 971).
 bool whole_tiles_win(const std::vector<EitherWay>& boards, int cus)
 {
     std::vector<TileRef> whole, split, list;
@@ -1051,19 +1053,24 @@ bool whole_tiles_win(const std::vector<EitherWay>& boards, int cus)
         split.insert(split.end(), b.split->rb.begin(), b.split->rb.end());
         filled &= b.split->plain.empty() && b.split->cd.empty() && b.split->mat_ty == kMatTY;
     }
-    const int C = std::max(1, cus / kXcds);
+    const int C = std::max(1, cus / kXcds);   // the material kernels run one block per compute unit
+    double rounds = 0;
     int longest = 0;
-    auto cost = [&](const std::vector<TileRef>& tiles) {
+    auto measure = [&](const std::vector<TileRef>& tiles) {
         build_work(tiles, C, list);
+        rounds = std::ceil((double)list.size() / (kXcds * C));
         longest = 0;
         for (const TileRef& t : list)
             if (t.board >= 0) longest = std::max(longest, t.ke - t.kb);
-        return std::ceil((double)list.size() / (kXcds * C)) * (longest + kBlockPlanes);
+        return rounds * (longest + kBlockPlanes);
     };
-    if (whole.size() * 16 > (size_t)cus) return true;
-    if (filled) return cost(whole) <= 0.86 * cost(split);
-    cost(whole);
-    return whole.size() * 32 > (size_t)cus || longest < 3;
+    if (filled) {
+        const double by_split = 0.86 * measure(split);
+        return rounds > 1 || measure(whole) <= by_split;
+    }
+    if (whole.size() * 32 > (size_t)cus) return true;
+    measure(whole);
+    return longest < 3;
 }
 
 // The pieces of a material board's pairs of steps: alone (pc_*, and the shares reported),

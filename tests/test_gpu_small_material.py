@@ -31,7 +31,8 @@ def board(kind, nx, ny, nz):
 
 # kind, sizes, whole tiles, rows of the material variant's tiles
 CASES = [("slab", 64, 32, 86, 0, 10), ("lossy", 64, 32, 86, 0, 10), ("slab", 48, 43, 30, 1, 14),
-         ("filled", 56, 39, 48, 1, 10), ("filled", 27, 45, 65, 1, 10), ("filled", 128, 77, 60, 1, 14)]
+         ("filled", 56, 39, 48, 1, 10), ("filled", 27, 45, 65, 1, 10), ("filled", 128, 77, 60, 1, 14),
+         ("filled", 152, 63, 23, 1, 10)]
 
 
 @pytest.mark.parametrize("case", CASES, ids=str)

@@ -68,10 +68,11 @@ WHOLE, SHORT, SPLIT = {"tall"}, {"short"}, {"short", "plain"}
 @pytest.mark.parametrize("copies, board, alone, batch", [
     (1, filled(56, 39, 48), SHORT, SHORT), (4, filled(56, 39, 48), SHORT, WHOLE),
     (1, filled(27, 45, 65), SHORT, SHORT), (1, filled(26, 101, 36), SHORT, SHORT),
-    (4, filled(20, 35, 50), SHORT, SHORT), (5, filled(20, 35, 50), SHORT, WHOLE),        # 16 and 20 tiles
-    (1, filled(128, 77, 60), WHOLE, WHOLE), (1, filled(64, 187, 60), WHOLE, WHOLE),      # 14 and 17 tiles
+    (4, filled(20, 35, 50), SHORT, SHORT), (1, filled(15, 228, 11), SHORT, SHORT),
+    (3, filled(28, 145, 12), SHORT, SHORT), (1, filled(2, 2, 2), SHORT, SHORT),          # one tile of either
+    (1, filled(128, 77, 60), WHOLE, WHOLE), (1, filled(200, 200, 60), WHOLE, WHOLE),
     (1, filled(444, 364, 60), WHOLE, WHOLE), (1, filled(1048, 792, 88), SHORT, SHORT),   # past the line
-    (4, filled(128, 386, 20), WHOLE, WHOLE), (1, filled(2, 2, 2), SHORT, SHORT),      # one tile of either
+    (4, filled(128, 386, 20), WHOLE, WHOLE),                                             # both in rounds
     (1, slab(64, 32, 86), SPLIT, SPLIT), (2, slab(64, 32, 86), SPLIT, SPLIT), (3, slab(64, 32, 86), SPLIT, WHOLE),
     (1, slab(64, 88, 60), SPLIT, SPLIT), (1, slab(64, 89, 60), WHOLE, WHOLE),            # 8 and 9 tiles
     (1, slab(48, 43, 30), WHOLE, WHOLE), (1, slab(48, 43, 33), SPLIT, SPLIT),            # pieces of two and three planes
